@@ -341,20 +341,15 @@ int lbm_load(lbm_handle* h, const char* path);
  * summed kernel time (ms) and launch count since timing was switched on. */
 int lbm_set_kernel_timing(lbm_handle* h, int on);
 int lbm_kernel_time(lbm_handle* h, double* ms, int64_t* launches);
-/* Launch shape of the stream-collide kernel: workgroup size 128, 256 or 512
- * nodes; whether workgroups are remapped so that each of the 8 XCDs streams
- * one contiguous range of the grid; and, with swimmers, `resident` > 0 makes
- * the launch that runs concurrently with the immersed-boundary kernels
- * persistent with that many workgroups per compute unit (0: one workgroup
- * per block; -1: no concurrency, the immersed-boundary kernels then one
- * full-grid launch).  With FP32 storage (either form) the persistent
- * workgroups of each XCD claim that XCD's blocks one at a time from a device
- * counter; with FP16 storage they walk them in a fixed order.  An XCD's
- * blocks are one contiguous range when remapped, every eighth block
- * otherwise.  Results are bitwise identical for every shape.  Defaults (the
- * fastest measured on MI355X): one box with FP32 storage 512 / no remap / 1;
- * FP16 storage 256 / no remap / 2; batches 512 / no remap / 0.
- * Errors: LBM_EINVAL. */
+/* Launch shape of the stream-collide kernel without swimmers and in the serial
+ * order: workgroup size 128, 256 or 512 nodes; whether workgroups are remapped
+ * so that each of the 8 XCDs streams one contiguous range of the grid.  With
+ * swimmers `resident` >= 0 (any value) runs the fused step, two launches of
+ * 512-thread workgroups that hold the immersed-boundary work and the
+ * stream-collide of all blocks side by side; -1 runs the immersed-boundary
+ * work by itself and then one full-grid launch of the given shape.  Results
+ * are bitwise identical for every choice.  Defaults: 512 (256 with FP16
+ * storage) / no remap / fused.  Errors: LBM_EINVAL. */
 int lbm_set_stream_collide_launch(lbm_handle* h, int block, int xcd_remap, int resident);
 /* Algorithmic bytes one stream-collide launch moves (19 populations read and
  * written once per node at the storage width). */

@@ -4,12 +4,12 @@
 // The forward run is plain stepping (lbm_step) with the populations, markers
 // and bead statistics copied aside every K steps.  Segments are then taken in
 // reverse order: the segment's forward steps are recomputed from its
-// checkpoint on scratch buffers (lbm_step's concurrent bulk / near-block
-// schedule, so the trajectory is bitwise the forward one), keeping per step the markers, the
+// checkpoint on scratch buffers (lbm_step's fused launches, so the trajectory
+// is bitwise the forward one), keeping per step the markers, the
 // bead statistics, the marker forces, the force density with its tile stamps
 // and (rho, u) of every node; then its reverse steps run from last to first.
 // Segment storage is double-buffered: the recompute of segment c - 1 runs on
-// its own pair of streams while the reverse sweep of segment c runs on the
+// its own stream while the reverse sweep of segment c runs on the
 // handle's stream and the adjoint side stream.
 // The handle's own state is only touched by the forward run.
 #include <hip/hip_runtime.h>
@@ -57,11 +57,13 @@ struct AdjWork {
   AdjSet set[2];
   float* L = nullptr;           // [2][19][pstride] adjoint populations
   float *lu = nullptr, *lF = nullptr;  // [3][pstride]
+  int* lstamp = nullptr;        // [ntiles] step whose lambda_u a tile holds
+  double* pos0 = nullptr;       // [3][nm] markers of a segment's first step
   int* overflow = nullptr;
   int nsc = 0, max_near = 0;
   hipStream_t side = nullptr;            // reverse sweep: side stream (main: the handle's)
-  hipStream_t rmain = nullptr, rside = nullptr;  // recompute
-  hipEvent_t ev[12] = {};  // 0-3, 8, 9: recompute; 4-7, 10, 11: reverse
+  hipStream_t rmain = nullptr;           // recompute
+  hipEvent_t ev[12] = {};  // 4-7, 10, 11: reverse
   hipEvent_t rec_done[2] = {}, rev_done[2] = {}, start = nullptr;
   // recompute graphs by (length, set); reverse-sweep graphs by (objective
   // swimmer, length, parity, set): the swimmer is a kernel argument of the
@@ -71,7 +73,7 @@ struct AdjWork {
   float* lr32 = nullptr;
 
   ~AdjWork() {
-    for (hipStream_t q : {side, rmain, rside})
+    for (hipStream_t q : {side, rmain})
       if (q) (void)hipStreamSynchronize(q);
     for (auto* g : {&rgraphs, &vgraphs})
       for (auto& kv : *g)
@@ -80,7 +82,7 @@ struct AdjWork {
       if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : {rec_done[0], rec_done[1], rev_done[0], rev_done[1], start})
       if (e) (void)hipEventDestroy(e);
-    for (hipStream_t q : {side, rmain, rside})
+    for (hipStream_t q : {side, rmain})
       if (q) (void)hipStreamDestroy(q);
     for (void* p : allocs) (void)hipFree(p);
   }
@@ -111,7 +113,8 @@ int ensure_work(lbm_handle* h, int64_t nck, int K) {
   w->ck_pop = w->alloc<float>((size_t)nck * kQ * ps, rc);
   w->ck_pos = w->alloc<double>((size_t)nck * 3 * nm, rc);
   w->ck_bst = w->alloc<BeadState>((size_t)nck * nb, rc);
-  // near-block bound of the scratch launches (as set_near_bounds, blocks of kScBlock)
+  // bound on the near blocks of kScBlock nodes: per bead the marked node box is its
+  // reserved tile span plus two nodes each side
   w->nsc = (int)((h->nodes + kScBlock - 1) / kScBlock);
   int64_t mx = 0;
   for (const Bead& b : h->beads) {
@@ -142,6 +145,8 @@ int ensure_work(lbm_handle* h, int64_t nck, int K) {
   w->L = w->alloc<float>(2 * kQ * ps, rc);
   w->lu = w->alloc<float>(3 * ps, rc);
   w->lF = w->alloc<float>(3 * ps, rc);
+  w->lstamp = w->alloc<int>((size_t)h->ntiles, rc);
+  w->pos0 = w->alloc<double>(3 * nm, rc);
   w->overflow = w->alloc<int>(1, rc);
   w->lr = w->alloc<double>(3 * nm, rc);
   w->lfm = w->alloc<double>(3 * nm, rc);
@@ -149,7 +154,7 @@ int ensure_work(lbm_handle* h, int64_t nck, int K) {
   w->bsum = w->alloc<double>(4 * nb, rc);
   w->grad = w->alloc<double>(4, rc);
   w->lr32 = w->alloc<float>(3 * nm, rc);
-  for (hipStream_t* q : {&w->side, &w->rmain, &w->rside})
+  for (hipStream_t* q : {&w->side, &w->rmain})
     if (!rc) rc = h->hip(hipStreamCreate(q), "hipStreamCreate");
   for (hipEvent_t& e : w->ev)
     if (!rc) rc = h->hip(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreateWithFlags");
@@ -180,18 +185,6 @@ Dev with_near(Dev d, const Dev& n) {
   return d;
 }
 
-// Advection of segment step i: markers of pslab[i] into pslab[i+1]; the
-// near-count reset of the advection kernel goes to a sink (every entry's
-// counts are cleared at segment start).
-Dev advect_view(const Dev& base, const AdjSet& S, int i, size_t nm) {
-  Dev d = base;
-  d.sub = i + 1;
-  d.pos = S.pslab + i * 3 * nm;
-  d.pos_next = S.pslab + (i + 1) * 3 * nm;
-  d.near_count = S.count_sink;
-  return d;
-}
-
 // The state view of a segment set: its populations, velocity, marker
 // velocities and step counter.
 Dev set_view(const Dev& dS, const AdjSet& S, size_t popn) {
@@ -204,59 +197,40 @@ Dev set_view(const Dev& dS, const AdjSet& S, size_t popn) {
   return d;
 }
 
-// Recompute of one segment from its checkpoint (already in the set), on the
-// streams s (main) and S2 (side): near marks of its first step, then the
-// steps as lbm_step's concurrent schedule -- the side stream advects step
-// i-1 and runs step i's bead statistics, forces, spreading and near-block
-// launch (after the bulk launch of step i-1), the main stream the bulk launch
-// of step i (after the near-block launch of step i-1).  Step i reads the
-// markers of pslab[i], advects them into pslab[i+1], writes its bead
-// statistics to bslab[i+1] taking the previous centres (the volume's
-// reference point) from bslab[i], and marks the near blocks of step i+1 into
-// entry i+1.
-void enqueue_recompute(lbm_handle* h, AdjWork& w, const AdjSet& St, const Dev& dS, int m, int nblocks,
-                       hipStream_t s, hipStream_t S2) {
+// Recompute of one segment from its checkpoint (already in the set) on stream
+// s: near marks of its first step, then the steps as lbm_step's fused launches.
+// Step i's markers go to pslab[i] (the checkpoint's, or advanced from
+// pslab[i-1]), its bead statistics to bslab[i+1], taking the previous centres
+// (the volume's reference point) from bslab[i]; it marks the near blocks of
+// step i+1 into entry i+1.
+void enqueue_recompute(lbm_handle* h, AdjWork& w, const AdjSet& St, const Dev& dS, int m, hipStream_t s) {
   const size_t ps = (size_t)h->pstride, nm = (size_t)h->nm, nb = h->beads.size();
-  hipEvent_t* ev = w.ev;
   {
-    // near marks of the segment's first step from the checkpoint's markers
-    // (into entry 0), bead statistics discarded
+    // marks of the segment's first step from the checkpoint's markers (near
+    // blocks into entry 0), bead statistics discarded
     Dev d = near_view(dS, w, St, 0);
     d.pos = St.pslab;
     d.bstate_prev = St.bslab;
     d.bstate = St.bsink;
     launch_bead_stats(d, -1, s);
+    launch_bead_stats(d, kMarkTiles, s);
   }
-  (void)hipEventRecord(ev[8], s);
-  (void)hipStreamWaitEvent(S2, ev[8], 0);
+  const int share = step_share(h);
   for (int i = 0; i < m; ++i) {
-    Dev d = dS;
+    Dev d = near_view(dS, w, St, i + 1);
     d.sub = i;
-    d.pos = St.pslab + i * 3 * nm;
-    d.bstate_prev = St.bslab + i * nb;
-    d.bstate = St.bslab + (i + 1) * nb;
     d.fm = St.fslab + i * 3 * nm;
     d.F = St.Fslab + (size_t)i * 3 * ps;
     d.stamp = St.stslab + (size_t)i * h->ntiles;
     d.mom = St.mom + (size_t)i * h->nodes;
-    hipEvent_t bulk_now = ev[i & 1], bulk_prev = ev[(i + 1) & 1];
-    hipEvent_t near_now = ev[2 + (i & 1)], near_prev = ev[2 + ((i + 1) & 1)];
-    if (i > 0) launch_interp_advance(advect_view(dS, St, i - 1, nm), S2);
-    const Dev dm = with_near(d, near_view(dS, w, St, i + 1));
-    launch_stats_forces(dm, 0, S2);
-    launch_spread(dm, S2);
-    launch_marker_force_total(dm, dm.fm, S2);  // the step's total forces, read by the reverse sweep
-    const Dev dr = with_near(d, near_view(dS, w, St, i));
-    if (i > 0) (void)hipStreamWaitEvent(s, near_prev, 0);
-    launch_stream_collide_mom(dr, kLaunchBulk, nblocks, s);
-    (void)hipEventRecord(bulk_now, s);
-    if (i > 0) (void)hipStreamWaitEvent(S2, bulk_prev, 0);
-    launch_stream_collide_mom(dr, kLaunchActive, nblocks, S2);
-    (void)hipEventRecord(near_now, S2);
+    d.bstate = St.bslab + i * nb;
+    d.pos = St.pslab + (i > 0 ? i - 1 : 0) * 3 * nm;
+    d.pos_new = i > 0 ? St.pslab + i * 3 * nm : w.pos0;
+    launch_stream_collide_mom(d, i > 0 ? kLaunchStepA : kLaunchStepFirst, share, s);
+    d.bstate = St.bslab + (i + 1) * nb;
+    d.pos = St.pslab + i * 3 * nm;
+    launch_stream_collide_mom(d, kLaunchStepB, share, s);
   }
-  launch_interp_advance(advect_view(dS, St, m - 1, nm), S2);
-  (void)hipEventRecord(ev[9], S2);
-  (void)hipStreamWaitEvent(s, ev[9], 0);
 }
 
 // Reverse steps of a segment, last to first, on the streams s (main) and S2
@@ -279,7 +253,7 @@ void enqueue_reverse(lbm_handle* h, AdjWork& w, const AdjSet& St, const Dev& dS,
     d.bstate = St.bslab + (i + 1) * nb;
     d.fm = St.fslab + i * 3 * nm;
     d.F = St.Fslab + (size_t)i * 3 * ps;  // F_n, kept by the recompute
-    d.stamp = St.stslab + (size_t)i * h->ntiles;
+    d.stamp = w.lstamp;  // the tiles of lambda_u, stamped by its spreading
     const Dev dr = with_near(d, near_view(dS, w, St, i));
     a.Lsrc = w.L + ((n + 1) & 1) * popn;
     a.Ldst = w.L + (n & 1) * popn;
@@ -389,6 +363,11 @@ int run(lbm_handle* h, const lbm_adjoint_desc* ad, double* J, double* grad) {
       rc = h->hip(hipMemsetAsync(St.nflag, 0x80, sizeof(int) * (size_t)(K + 1) * kNearSlots * w.nsc, s),
                   "hipMemsetAsync");
   }
+  if (!rc) rc = h->hip(hipMemsetAsync(w.lstamp, 0x80, sizeof(int) * (size_t)h->ntiles, s), "hipMemsetAsync");
+  // the recompute marks near tiles in the handle's arrays: the forward run's
+  // marks of the same steps go first, and stepping marks its own anew afterwards
+  if (!rc) rc = clear_near(h, s);
+  h->need_prologue = true;
   if (!rc) rc = h->hip(hipMemsetAsync(w.overflow, 0, sizeof(int), s), "hipMemsetAsync");
   if (rc) return rc;
   launch_adj_init(set_view(dS, w.set[0], popn), a, s);
@@ -416,7 +395,7 @@ int run(lbm_handle* h, const lbm_adjoint_desc* ad, double* J, double* grad) {
     launch_set_step(St.step, n0, r);
     const Dev dv = set_view(dS, St, popn);
     e = enqueue_or_replay(h, w.rgraphs, 4 * (int64_t)m + k, r,
-                          [&] { enqueue_recompute(h, w, St, dv, m, nblocks, r, w.rside); });
+                          [&] { enqueue_recompute(h, w, St, dv, m, r); });
     if (!e) e = h->hip(hipEventRecord(w.rec_done[k], r), "hipEventRecord");
     return e;
   };

@@ -32,11 +32,11 @@ __host__ __device__ constexpr int spread_parts(int nbeads) {
   return nbeads <= kWideBeads ? kSpreadPartsWide : kSpreadPartsNarrow;
 }
 constexpr int kScBlock = 256;  // stream-collide threads per block
-// Near-block flags hold three step slots (step mod 3): the bead statistics of
-// step n mark slot n mod 3 while the bulk launch of step n - 1, which may
-// still be running, reads slot (n - 2) mod 3.  Lists and counts, read only by
-// the near-block launch that precedes the next marking on the same stream,
-// keep two (step parity).
+// Near-block flags (two-stream schedule, reverse sweep of the
+// adjoint) hold three step slots (step mod 3): marks of step n go to slot n mod
+// 3 while the bulk launch of step n - 1, which may still be running, reads slot
+// (n - 2) mod 3.  Lists and counts, read only by the near-block launch that
+// precedes the next marking on the same stream, keep two (step parity).
 constexpr int kNearSlots = 3;
 
 // Store of a streamed population value, written through: a relaxed atomic
@@ -56,20 +56,34 @@ __device__ inline void stream_store(unsigned short* p, unsigned short v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 constexpr int64_t kWriteThroughBytes = int64_t(1) << 30;  // both population sets
+constexpr int64_t kLastLevelCache = int64_t(256) << 20;
 __host__ __device__ inline int near_slot(int64_t v) {
   const int r = (int)(v % kNearSlots);
   return r < 0 ? r + kNearSlots : r;
 }
+// Fused step: workgroup size, nodes owned by a surface patch, bounds on its
+// local nodes, elements and volume triangles, partial statistics per patch, nodes the near tiles reach beyond a
+// bead's region, beads and patch values of a box a spreading workgroup folds.
+constexpr int kStepBlock = 512;
+constexpr int kPatchOwn = 32;
+constexpr int kPatchLocal = 160;
+constexpr int kPatchTri = 192;
+constexpr int kPatchHinge = 288;
+constexpr int kPatchVol = 128;
+constexpr int kPartVals = 12;
+constexpr int kSlabLayers = 2;       // z layers of a spreading slab
+constexpr int kSlabParts = kTile / kSlabLayers;
+constexpr int kNearMargin = 2;
+constexpr int kFoldBeads = 64;
+constexpr int kSlabWorkers = 64;  // spreading workgroups per bead at most
+constexpr int kFoldPatches = 256;
 constexpr int kPopBlock = 256; // nodes per population block (a power of two: shifts and masks)
-// mark_offset of launch_bead_stats that leaves the near blocks unmarked (the
-// near-block launch of the concurrent schedule marks them instead)
-constexpr int kNoMark = -(1 << 30);
-// Block counters of the persistent bulk launch: one per XCD (workgroups are
-// dealt to the 8 XCDs round robin) and step parity, each on its own 128-byte
-// line; Dev::work holds kWorkCounters ints.
-constexpr int kXcds = 8;
-constexpr int kWorkStride = 32;
-constexpr int kWorkCounters = 2 * kXcds * kWorkStride;
+// mark_offset of launch_bead_stats / launch_stats_forces that leaves the near
+// blocks unmarked (the near-block launch marks them)
+constexpr int kNoMark = -(1 << 30) + 1;
+// mark_offset of launch_bead_stats that marks the near tiles of the fused step
+// instead of near blocks
+constexpr int kMarkTiles = -(1 << 30);
 
 // Element index of population q of global node `node`.  A wavefront's 64
 // consecutive nodes read or write one contiguous 256-byte (FP32) run per
@@ -89,7 +103,8 @@ constexpr int kLatticeC[kQ][3] = {{0, 0, 0},  {1, 0, 0},  {-1, 0, 0}, {0, 1, 0},
                                   {-1, 1, 0}, {1, 0, 1},  {-1, 0, -1}, {1, 0, -1}, {-1, 0, 1},
                                   {0, 1, 1},  {0, -1, -1}, {0, 1, -1}, {0, -1, 1}};
 __host__ __device__ constexpr int opposite(int q) { return q == 0 ? 0 : ((q & 1) ? q + 1 : q - 1); }
-enum ScLaunch { kLaunchAll = 0, kLaunchBulk = 1, kLaunchActive = 2 };
+enum ScLaunch { kLaunchAll = 0, kLaunchBulk = 1, kLaunchActive = 2, kLaunchStepFirst = 3, kLaunchStepA = 4,
+                kLaunchStepB = 5, kLaunchStepSpread = 6 };
 
 // Division of unsigned 32-bit numbers by an invariant d >= 1 through a
 // multiply-high and two shifts (Granlund and Montgomery, "Division by
@@ -126,6 +141,7 @@ struct Box {
   float tau, omega;     // tau and 1/tau
   float gx, gy, gz;     // uniform body force density
   Divisor div_nx, div_ny;  // node id -> (x, y, z) without integer division
+  double inv[3];           // 1 / nx, 1 / ny, 1 / nz (wrap)
 };
 
 // Per-bead constant data.
@@ -136,8 +152,10 @@ struct Bead {
   int slot;             // 0, 1, 2 within the swimmer
   int tiles_x, tiles_y, tiles_z;  // reserved candidate tiles per axis
   int tile_block0;      // first spread block of this bead
+  int patch0, npatch;   // surface patches of the fused step (Dev::patch)
   float ks, C, kt, kv;  // Skalak ks and C, Kantor-Nelson kt = 2 kb/sqrt 3, kv
   double V0;            // stress-free volume
+  double inv_nv;        // 1 / nv
 };
 
 struct Swimmer {
@@ -161,6 +179,19 @@ struct BeadState {
 struct BeadTerms {
   float pv;
   float share[3];
+};
+
+// Near tiles of a bead: a run of tiles per axis (first tile in the box, count,
+// periodic) holding every node within kNearMargin nodes of the bead's region.
+struct NearRange {
+  int t0[3], cnt[3];
+};
+
+// Per box: its beads, surface patches and markers, its part of the slab list
+// (first entry) and the number of its spreading workgroups.
+struct StepBox {
+  int bead0, nbeads, patch0, npatch;
+  int m0, m_end, list0, workers;
 };
 
 // Everything a kernel needs, passed by value.
@@ -219,18 +250,16 @@ struct Dev {
   // h*4 + role, vertex ids x1 x2 x3 x4); element -1 = idle lane
   const int* lane_elem;  // [nm * 32]
   const int4* lane_v;    // [nm * 32]
-  // stream-collide blocks near the swimmers: flags near[step mod 3][block] =
-  // step that marked the block, and per-parity block lists
-  // (near_list[parity][i], near_count[parity]); a block is near when it holds
-  // a node within two nodes of a bead's stencil region
+  // blocks of sc_bs nodes near the swimmers (two-stream schedule, reverse sweep
+  // of the adjoint): flags
+  // near[step mod 3][block] = step that marked the block, and per-parity block
+  // lists (near_list[parity][i], near_count[parity]); a block is near when it
+  // holds a node within two nodes of a bead's stencil region.  Null elsewhere.
   int* near;
-  // persistent bulk launch: block counters work[parity][group * kWorkStride]
-  // (zero before a step's launch; each launch zeroes the next step's)
-  int* work;
   int* near_list;
   int* near_count;
   int max_near, nsc, sc_bs;
-  // nonzero in the near-block launch of the concurrent schedule: nbeads extra
+  // nonzero in the near-block launch of the two-stream schedule: nbeads extra
   // workgroups mark the near blocks of the next step from the bead regions of
   // this step (mark_near_blocks), off the bead-statistics kernel's path, and
   // further ones form each marker's total force (fm)
@@ -251,6 +280,36 @@ struct Dev {
   // the tile's offset within the bead's reserved tiles and which part
   // (kTile / spread_parts(beads) z layers) of the tile the block fills
   const int4* spread_info;
+  // ---- fused step (step_kernels.hip): two launches per step on one stream ----
+  // Surface patches: each bead's nodes split into compact groups of at most
+  // kPatchOwn.  A patch's local nodes are its own, then the others its
+  // elements touch; local ids index the patch's LDS copy of the positions.
+  const int4* patch;        // {bead, box, own nodes | local nodes << 16, triangles | hinges << 16}
+  const int* patch_marker;  // [npatch][kPatchLocal] marker of each local node
+  const int2* patch_tri;    // [npatch][kPatchTri] {triangle, three 10-bit local ids}
+  const int4* patch_hinge;  // [npatch][kPatchHinge] {hinge, four 16-bit local ids, 0}
+  // [npatch][kPatchOwn * 32]: the force lanes of the own nodes as places in the
+  // patch's element results, 3 * triangle + corner (lanes 0..7) or
+  // 4 * hinge + role (lanes 8..31); -1: idle
+  const int* patch_lane;
+  const int* patch_vol;     // [npatch][kPatchVol] three 10-bit local ids; -1: none
+  int npatch;
+  double* pos_new;          // [3][nm] marker positions of the step in progress
+  double* part;             // [npatch][kPartVals]: sums x y z, min x y z, max x y z, 6 V in two parts
+  double2* drive;           // [nswimmers] driving forces f1, f3 of the step
+  NearRange* near_range;    // [2][nbeads], slot = step parity
+  int* near_tile;           // [2][ntiles] step for which the tile is near
+  int* step_near;           // [2][nstep] step for which the block holds a near tile
+  int ntiles, nstep;
+  const int* step_block_box;   // block of kStepBlock nodes -> box (batches)
+  const int* step_box_block0;  // first such block of each box
+  const StepBox* step_box;     // [nboxes]
+  const int2* step_spread;     // spreading workgroup -> {box, index in the box} (batches)
+  int4* slab_list;             // slabs of the step, box after box (k_step_a's list workgroups)
+  int* slab_count;             // [nboxes]
+  int step_spread_blocks;
+  int folded;               // 1: the bead terms come from k_step_fold
+  int tick;                 // steps the closing advection adds to the step counter
   // (rho, u) of every node, written by the moment-recording stream-collide
   // variant only (segment recompute of the adjoint)
   float4* mom;
@@ -267,13 +326,18 @@ struct Dev {
 };
 
 // Launch wrappers (defined in the .hip files).
-// ev0 / ev1 (optional): events stamped by the launch's own dispatch packet
+// ev0 / ev1 (optional): events stamped by the launch's own dispatch packet.
+// Modes: kLaunchAll the full grid of nblocks workgroups of `block` nodes (each
+// XCD one contiguous range when `remap`); the launches of the fused step
+// (step_kernels.hip): kLaunchStepA, or kLaunchStepFirst where the markers are
+// not to be advanced first, takes the first `nblocks` blocks of the walk over
+// the grid and kLaunchStepB the rest, kLaunchStepSpread only spreads (no node
+// is collided).  `block`, `remap`, `resident` and `ncu` are not used there.
 void launch_stream_collide(const Dev& d, int storage, int mode, int block, int nblocks, int remap,
                            int resident, int ncu, hipStream_t s, hipEvent_t ev0 = nullptr,
                            hipEvent_t ev1 = nullptr);
-// Stream-collide (FP32 storage, single box, workgroups of kScBlock nodes,
-// launch mode kLaunchAll / kLaunchBulk / kLaunchActive) that also writes each
-// node's (rho, u_x, u_y, u_z) to d.mom; nblocks = node blocks of the box.
+// Stream-collide (FP32 storage, single box) that also writes each
+// node's (rho, u_x, u_y, u_z) to d.mom, in the step modes above.
 void launch_stream_collide_mom(const Dev& d, int mode, int nblocks, hipStream_t s);
 void launch_tick(const Dev& d, int count, hipStream_t s);
 void launch_velocity(const Dev& d, int storage, int nblocks, float* u_out, float* rho_out,
@@ -293,7 +357,8 @@ void launch_conserved(const Dev& d, int storage, int box, double* partial, int n
 constexpr int kNoAllocParts = 4096;
 hipError_t resolve_conserved_scratch(int device, double** out);
 // mark_offset: the near blocks of step (counter + sub + mark_offset) are
-// marked from the new bead regions; kNoMark: not marked.
+// marked from the new bead regions; kMarkTiles: the near tiles of step
+// counter + sub (the fused step's).
 void launch_bead_stats(const Dev& d, int mark_offset, hipStream_t s);
 // bead statistics and the split membrane forces (independent of each other),
 // in one launch for handles of at most kWideBeads beads
@@ -301,6 +366,8 @@ void launch_stats_forces(const Dev& d, int mark_offset, hipStream_t s);
 // total marker forces of step counter + sub from the split parts into out
 void launch_marker_force_total(const Dev& d, float* out, hipStream_t s);
 void launch_spread(const Dev& d, hipStream_t s);
+// Interpolation and advection.  d.tick > 0: closes a sequence of d.tick fused
+// steps, advancing the step counter too.
 void launch_interp_advance(const Dev& d, hipStream_t s);
 void launch_bead_centres(const Dev& d, double* out, hipStream_t s);
 void launch_copy(const void* src, void* dst, int64_t bytes, hipStream_t s);

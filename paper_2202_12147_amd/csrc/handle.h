@@ -57,6 +57,7 @@ struct lbm_handle {
   // host model
   std::vector<Box> boxes;
   std::vector<Bead> beads;
+  std::vector<double> bead_radius;
   std::vector<Swimmer> swimmers;
   std::vector<double> pos0;  // [nm][3] initial marker positions
   std::vector<int> marker_bead;
@@ -89,6 +90,7 @@ struct lbm_handle {
   lbmib::BeadTerms* d_bterms = nullptr;  // [beads]
   Bead* d_beads = nullptr;
   BeadState* d_bstate = nullptr;
+  BeadState* d_bmark = nullptr;    // bead regions of the markers when stepping resumes
   Swimmer* d_swimmers = nullptr;
   int *d_marker_bead = nullptr, *d_tri = nullptr, *d_hinge = nullptr;
   int4* d_marker_info = nullptr;
@@ -97,10 +99,8 @@ struct lbm_handle {
   int *d_lane_elem = nullptr, *d_lane_v = nullptr;
   int* d_overflow = nullptr;
   int* d_spread_info = nullptr;  // [spread block][8], see Dev::spread_info
-  int *d_near = nullptr, *d_near_list = nullptr, *d_near_count = nullptr;
-  int* d_work = nullptr;           // persistent bulk block counters (kWorkCounters)
   bool need_prologue = true;
-  hipStream_t side = nullptr;      // IBM chain, forked from `stream` every step
+  hipStream_t side = nullptr;      // two-stream schedule: the markers' chain, forked from `stream` every step
   std::vector<hipEvent_t> step_events;  // per chunk step: bulk done, near blocks done; + one fork
   double *d_partial = nullptr, *d_out = nullptr, *d_centres = nullptr;
   double* conserved_scratch = nullptr;  // the device's static scratch (not owned)
@@ -137,6 +137,9 @@ namespace lbmib {
 namespace rt {
 
 int element_bytes(const lbm_handle* h);
+// Blocks of a fused step's first launch; clearing of the near-tile marks.
+int step_share(const lbm_handle* h);
+int clear_near(lbm_handle* h, hipStream_t s);
 // Device buffers and mesh tables, once, before the first step.
 int upload(lbm_handle* h);
 // Bead regions and near blocks of the current markers when stepping resumes.

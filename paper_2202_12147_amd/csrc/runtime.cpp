@@ -3,6 +3,7 @@
 // graphs), observables and checkpoints.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -111,12 +112,21 @@ float lattice_weight(int q) { return q == 0 ? 1.0f / 3.0f : (q < 7 ? 1.0f / 18.0
 
 // Candidate tiles reserved per axis for a bead: the node span of its stencils
 // with 25% room for deformation, in tiles, for any alignment.
-int reserved_tiles(double radius, int width, int n, int T) {
-  const int span = (int)std::floor(2.0 * radius * 1.25) + width + 2;
+int reserved_tiles(double radius, int width, int margin, int n, int T) {
+  const int span = (int)std::floor(2.0 * radius * 1.25) + width + 2 + 2 * margin;
   // an edge that is not a whole number of tiles ends in a short tile, which a
   // run of nodes across it may touch on top of the whole tiles
   const int shorter = n % kTile ? 1 : 0;
   return std::min(T, (span + kTile - 2) / kTile + 1 + shorter);
+}
+
+// A bead's reserved tiles; `margin`: nodes kept around its region (the near tiles
+// of the fused step).
+void reserve_tiles(const lbm_handle* h, Bead& b, double radius, int margin) {
+  const Box& B = h->boxes[b.box];
+  b.tiles_x = reserved_tiles(radius, h->width, margin, B.nx, B.tx);
+  b.tiles_y = reserved_tiles(radius, h->width, margin, B.ny, B.ty);
+  b.tiles_z = reserved_tiles(radius, h->width, margin, B.nz, B.tz);
 }
 
 // Host layout of population deviations: box after box, each [19][n_box];
@@ -206,6 +216,185 @@ void set_near_bounds(lbm_handle* h) {
   d.max_near = (int)std::max<int64_t>(1, std::min<int64_t>(mx, d.nsc));
 }
 
+// Handles with swimmers that step on the two-stream schedule rather than with
+// the fused launches (step_kernels.hip):
+//  - FP16 storage: the fused step sums forces and interpolated velocities in
+//    another order, and with half-precision populations one changed last bit of
+//    a force changes which way populations are rounded, so the velocity field
+//    of a run would move by 1e-4 (its own distance from the FP64 result) against
+//    its earlier values.
+//  - batches of many beads: there the number of the markers' workgroups decides,
+//    not their latency, and the fused step's patches advance their border nodes
+//    twice (32 boxes, 11.8 M nodes: 441 us per step against 522 fused; 24 boxes,
+//    72 beads: 201 and 199; 16 boxes: 254 and 237).
+constexpr int kFusedBatchBeads = 64;
+bool two_stream(const lbm_handle* h) {
+  if (h->swimmers.empty()) return false;
+  return h->storage == LBM_FP16_SHIFTED || (h->boxes.size() > 1 && h->beads.size() > (size_t)kFusedBatchBeads);
+}
+
+// ---- surface patches (Dev::patch) ------------------------------------------------
+struct Patches {
+  std::vector<int> head;    // [npatch][4], see Dev::patch
+  std::vector<int> marker;  // [npatch][kPatchLocal]
+  std::vector<int> tri;     // [npatch][kPatchTri][2]
+  std::vector<int> hinge;   // [npatch][kPatchHinge][4]
+  std::vector<int> lane;    // [npatch][kPatchOwn * 32]
+  std::vector<int> vol;     // [npatch][kPatchVol]
+};
+
+// Split the markers `ids` into `parts` compact groups of nearly equal size:
+// halves (by part count) along the longest axis of their bounding box.
+void split_markers(const std::vector<double>& pos, std::vector<int> ids, int parts, std::vector<std::vector<int>>& out) {
+  if (parts <= 1) {
+    out.push_back(std::move(ids));
+    return;
+  }
+  int axis = 0;
+  double best = -1;
+  for (int a = 0; a < 3; ++a) {
+    double lo = 1e300, hi = -1e300;
+    for (int m : ids) {
+      lo = std::min(lo, pos[3 * (size_t)m + a]);
+      hi = std::max(hi, pos[3 * (size_t)m + a]);
+    }
+    if (hi - lo > best) {
+      best = hi - lo;
+      axis = a;
+    }
+  }
+  const int left = parts / 2;
+  const size_t cut = ids.size() * left / parts;
+  std::sort(ids.begin(), ids.end(), [&](int a, int b) {
+    const double x = pos[3 * (size_t)a + axis], y = pos[3 * (size_t)b + axis];
+    return x < y || (x == y && a < b);
+  });
+  split_markers(pos, std::vector<int>(ids.begin(), ids.begin() + cut), left, out);
+  split_markers(pos, std::vector<int>(ids.begin() + cut, ids.end()), parts - left, out);
+}
+
+// Patches of every bead from the per-node lane tables (lane_elem, lane_v).
+// False when a patch exceeds the fixed table strides, which no icosphere's does.
+// Beads of the same refinement have the same mesh, so the first one's tables
+// serve the others with their own marker and element offsets.
+bool build_patches(lbm_handle* h, const std::vector<int>& lane_elem, const std::vector<int>& lane_v, Patches& P) {
+  std::unordered_map<int, size_t> built;  // mesh nodes -> first bead with such a mesh
+  for (Bead& Bd : h->beads) {
+    const auto same = built.emplace(Bd.nv, (size_t)(&Bd - h->beads.data()));
+    if (!same.second) {
+      const Bead& F = h->beads[same.first->second];
+      Bd.patch0 = (int)P.head.size() / 4;
+      Bd.npatch = F.npatch;
+      auto copy = [&](std::vector<int>& v, size_t stride) {
+        const size_t from = v.size();
+        v.resize(from + stride * F.npatch);
+        std::copy_n(v.begin() + stride * F.patch0, stride * F.npatch, v.begin() + from);
+        return v.begin() + from;
+      };
+      auto head = copy(P.head, 4);
+      auto marker = copy(P.marker, kPatchLocal);
+      auto tri = copy(P.tri, 2 * kPatchTri);
+      auto hinge = copy(P.hinge, 4 * kPatchHinge);
+      copy(P.lane, kPatchOwn * 32);
+      copy(P.vol, kPatchVol);
+      const int dm = Bd.first - F.first, dt = Bd.tri0 - F.tri0, dh = dt / 2 * 3;  // 3/2 hinges per triangle
+      for (int p = 0; p < F.npatch; ++p) {
+        head[4 * p] = (int)(&Bd - h->beads.data());
+        head[4 * p + 1] = Bd.box;
+        for (int i = 0; i < kPatchLocal; ++i) marker[(size_t)p * kPatchLocal + i] += dm;
+        for (int i = 0; i < kPatchTri; ++i) tri[2 * ((size_t)p * kPatchTri + i)] += dt;
+        for (int i = 0; i < kPatchHinge; ++i) hinge[4 * ((size_t)p * kPatchHinge + i)] += dh;
+      }
+      continue;
+    }
+    // split on the unit mesh: the patches, and with them the order of every sum,
+    // are the same for all beads of a refinement, wherever they lie
+    int level = 0;
+    while (10 * (1 << 2 * level) + 2 < Bd.nv) ++level;
+    std::vector<int> ids(Bd.nv);
+    for (int i = 0; i < Bd.nv; ++i) ids[i] = i;
+    std::vector<std::vector<int>> groups;
+    split_markers(icosphere(level).v, ids, (Bd.nv + kPatchOwn - 1) / kPatchOwn, groups);
+    for (auto& g : groups)
+      for (int& m : g) m += Bd.first;
+    Bd.patch0 = (int)P.head.size() / 4;
+    Bd.npatch = (int)groups.size();
+    std::vector<int> group_of(Bd.nv);
+    for (size_t g = 0; g < groups.size(); ++g)
+      for (int m : groups[g]) group_of[m - Bd.first] = (int)g;
+    // each triangle's volume term goes to the emptiest of its corners' patches
+    std::vector<std::vector<int>> tris(groups.size());
+    for (int t = Bd.tri0; t < Bd.tri0 + Bd.ntri; ++t) {
+      int best = -1;
+      for (int k = 0; k < 3; ++k) {
+        const int g = group_of[h->tri[3 * (size_t)t + k] - Bd.first];
+        if (best < 0 || tris[g].size() < tris[best].size()) best = g;
+      }
+      tris[best].push_back(t);
+    }
+    for (size_t g = 0; g < groups.size(); ++g) {
+      const std::vector<int>& own = groups[g];
+      std::unordered_map<int, int> local;
+      std::vector<int> order;
+      auto id_of = [&](int m) {
+        auto it = local.find(m);
+        if (it != local.end()) return it->second;
+        const int i = (int)order.size();
+        local.emplace(m, i);
+        order.push_back(m);
+        return i;
+      };
+      for (int m : own) id_of(m);
+      std::unordered_map<int, int> tri_at, hinge_at;  // element -> place in the patch
+      std::vector<int> tri, hinge, lane(kPatchOwn * 32, -1), vol(kPatchVol, -1);
+      if (own.size() > (size_t)kPatchOwn || tris[g].size() > (size_t)kPatchVol) return false;
+      for (size_t j = 0; j < own.size(); ++j)
+        for (int l = 0; l < 32; ++l) {
+          const size_t src = 32 * (size_t)own[j] + l;
+          if (lane_elem[src] < 0) continue;
+          const int* v = &lane_v[4 * src];
+          if (l < 8) {
+            const int t = lane_elem[src] / 3;
+            const auto at = tri_at.emplace(t, (int)tri.size() / 2);
+            if (at.second) {
+              tri.push_back(t);
+              const int a = id_of(v[0]), b = id_of(v[1]), c = id_of(v[2]);
+              tri.push_back(a | b << 10 | c << 20);
+            }
+            lane[32 * j + l] = 3 * at.first->second + lane_elem[src] % 3;
+          } else {
+            const int e = lane_elem[src] / 4;
+            const auto at = hinge_at.emplace(e, (int)hinge.size() / 4);
+            if (at.second) {
+              const int a = id_of(v[0]), b = id_of(v[1]), c = id_of(v[2]), f = id_of(v[3]);
+              const int rec[4] = {e, a | b << 16, c | f << 16, 0};
+              hinge.insert(hinge.end(), rec, rec + 4);
+            }
+            lane[32 * j + l] = 4 * at.first->second + lane_elem[src] % 4;
+          }
+        }
+      for (size_t i = 0; i < tris[g].size(); ++i) {
+        const int* c = &h->tri[3 * (size_t)tris[g][i]];
+        const int x = id_of(c[0]), y = id_of(c[1]), z = id_of(c[2]);
+        vol[i] = x | y << 10 | z << 20;
+      }
+      const int nt = (int)tri.size() / 2, nh = (int)hinge.size() / 4;
+      if (order.size() > (size_t)kPatchLocal || nt > kPatchTri || nh > kPatchHinge) return false;
+      const int head[4] = {(int)(&Bd - h->beads.data()), Bd.box, (int)own.size() | (int)order.size() << 16, nt | nh << 16};
+      P.head.insert(P.head.end(), head, head + 4);
+      order.resize(kPatchLocal, own[0]);
+      tri.resize(2 * kPatchTri, 0);      // unused places are not read
+      hinge.resize(4 * kPatchHinge, 0);
+      P.marker.insert(P.marker.end(), order.begin(), order.end());
+      P.tri.insert(P.tri.end(), tri.begin(), tri.end());
+      P.hinge.insert(P.hinge.end(), hinge.begin(), hinge.end());
+      P.lane.insert(P.lane.end(), lane.begin(), lane.end());
+      P.vol.insert(P.vol.end(), vol.begin(), vol.end());
+    }
+  }
+  return true;
+}
+
 int upload(lbm_handle* h) {
   if (h->uploaded) return LBM_OK;
   int rc = LBM_OK;
@@ -268,6 +457,9 @@ int upload(lbm_handle* h) {
     if (B.nbeads == 0) B.bead0 = (int)b;
     B.nbeads += 1;
   }
+  const bool fused = !two_stream(h);
+  if (fused)
+    for (size_t b = 0; b < h->beads.size(); ++b) reserve_tiles(h, h->beads[b], h->bead_radius[b], kNearMargin);
   // spread candidate blocks, spread_parts(beads) per reserved tile of each
   // bead (each kTile / parts z layers): {bead, box, first bead of the box,
   // beads of the box}, {tile offsets kx, ky, kz, part}
@@ -286,6 +478,41 @@ int upload(lbm_handle* h) {
           }
   }
   h->spread_blocks = (int)(spread_info.size() / 8);
+
+  // the fused step: surface patches, spreading workgroups and block tables
+  Patches P;
+  if (fused && !build_patches(h, lane_elem, lane_v, P)) return h->fail(LBM_EINVAL, "surface patch exceeds its tables");
+  const int npatch = (int)P.head.size() / 4;
+  std::vector<int> step_spread, step_owner, step_first(h->boxes.size());
+  std::vector<StepBox> step_box(h->boxes.size());
+  bool folded = false;
+  int64_t slabs = 0;
+  for (size_t i = 0; fused && i < h->boxes.size(); ++i) {
+    const Box& B = h->boxes[i];
+    StepBox& sx = step_box[i];
+    step_first[i] = (int)step_owner.size();
+    step_owner.insert(step_owner.end(), (size_t)((B.n + kStepBlock - 1) / kStepBlock), (int)i);
+    sx.list0 = (int)slabs;
+    if (B.nbeads == 0) continue;
+    const Bead &first = h->beads[B.bead0], &last = h->beads[B.bead0 + B.nbeads - 1];
+    sx.bead0 = B.bead0;
+    sx.nbeads = B.nbeads;
+    sx.patch0 = first.patch0;
+    sx.npatch = last.patch0 + last.npatch - first.patch0;
+    sx.m0 = first.first;
+    sx.m_end = last.first + last.nv;
+    if (B.nbeads > kFoldBeads || sx.npatch > kFoldPatches) folded = true;
+    int64_t mine = 0;
+    for (int b = B.bead0; b < B.bead0 + B.nbeads; ++b)
+      mine += (int64_t)h->beads[b].tiles_x * h->beads[b].tiles_y * h->beads[b].tiles_z * kSlabParts;
+    slabs += mine;
+    sx.workers = (int)std::min<int64_t>(mine, (int64_t)kSlabWorkers * B.nbeads);
+    for (int c = 0; c < sx.workers; ++c) {
+      const int e[2] = {(int)i, c};
+      step_spread.insert(step_spread.end(), e, e + 2);
+    }
+  }
+  const size_t nstep = step_owner.size();
 
   auto put = [&](void* dst, const void* src, size_t bytes) {
     if (rc != LBM_OK || bytes == 0) return;
@@ -313,15 +540,45 @@ int upload(lbm_handle* h) {
   h->d_lane_v = h->alloc<int>(lane_v.size(), rc);
   h->d_spread_info = h->alloc<int>(spread_info.size(), rc);
   h->d_centres = h->alloc<double>(3 * h->beads.size(), rc);
-  // near-block buffers, sized for the smallest stream-collide block (128):
-  // every box starts a new block, so the bound is the sum over the boxes of
-  // ceil(n / 128), not ceil(nodes / 128)
-  const int64_t nsc_max = h->sc_table_cap;
-  h->d_near = h->alloc<int>(kNearSlots * (size_t)nsc_max, rc);
-  h->d_near_list = h->alloc<int>(2 * (size_t)nsc_max, rc);
-  h->d_near_count = h->alloc<int>(2, rc);
-  h->d_work = h->alloc<int>(kWorkCounters, rc);
+  if (two_stream(h)) {
+    // near-block buffers, sized for the smallest stream-collide block (128):
+    // every box starts a new block, so the bound is the sum over the boxes of
+    // ceil(n / 128), not ceil(nodes / 128)
+    const int64_t nsc_max = h->sc_table_cap;
+    h->dev.near = h->alloc<int>(kNearSlots * (size_t)nsc_max, rc);
+    h->dev.near_list = h->alloc<int>(2 * (size_t)nsc_max, rc);
+    h->dev.near_count = h->alloc<int>(2, rc);
+  }
+  int* const d_patch = h->alloc<int>(P.head.size(), rc);
+  int* const d_patch_marker = h->alloc<int>(P.marker.size(), rc);
+  int* const d_patch_tri = h->alloc<int>(P.tri.size(), rc);
+  int* const d_patch_hinge = h->alloc<int>(P.hinge.size(), rc);
+  int* const d_patch_lane = h->alloc<int>(P.lane.size(), rc);
+  int* const d_patch_vol = h->alloc<int>(P.vol.size(), rc);
+  int* const d_step_spread = h->alloc<int>(step_spread.size(), rc);
+  StepBox* const d_step_box = h->alloc<StepBox>(step_box.size(), rc);
+  h->dev.slab_list = h->alloc<int4>((size_t)slabs, rc);
+  h->dev.slab_count = h->alloc<int>(h->boxes.size(), rc);
+  int* const d_step_owner = h->alloc<int>(nstep, rc);
+  int* const d_step_first = h->alloc<int>(step_first.size(), rc);
+  h->dev.pos_new = h->alloc<double>(3 * (size_t)nm, rc);
+  h->dev.part = h->alloc<double>((size_t)npatch * kPartVals, rc);
+  h->dev.drive = h->alloc<double2>(h->swimmers.size(), rc);
+  h->dev.near_range = h->alloc<NearRange>(2 * h->beads.size(), rc);
+  h->dev.near_tile = h->alloc<int>(2 * (size_t)h->ntiles, rc);
+  h->dev.step_near = h->alloc<int>(2 * nstep, rc);
+  h->d_bmark = h->alloc<BeadState>(h->beads.size(), rc);
   if (rc != LBM_OK) return h->fail(rc, "device allocation for markers failed");
+  put(d_patch, P.head.data(), sizeof(int) * P.head.size());
+  put(d_patch_marker, P.marker.data(), sizeof(int) * P.marker.size());
+  put(d_patch_tri, P.tri.data(), sizeof(int) * P.tri.size());
+  put(d_patch_hinge, P.hinge.data(), sizeof(int) * P.hinge.size());
+  put(d_patch_lane, P.lane.data(), sizeof(int) * P.lane.size());
+  put(d_patch_vol, P.vol.data(), sizeof(int) * P.vol.size());
+  put(d_step_spread, step_spread.data(), sizeof(int) * step_spread.size());
+  put(d_step_box, step_box.data(), sizeof(StepBox) * step_box.size());
+  put(d_step_owner, step_owner.data(), sizeof(int) * nstep);
+  put(d_step_first, step_first.data(), sizeof(int) * step_first.size());
   put(h->d_boxes, h->boxes.data(), sizeof(Box) * h->boxes.size());
   put(h->d_pos, pos.data(), sizeof(double) * pos.size());
   if (rc == LBM_OK && nm > 0) {
@@ -396,13 +653,24 @@ int upload(lbm_handle* h) {
   d.lane_v = reinterpret_cast<const int4*>(h->d_lane_v);
   d.spread_blocks = h->spread_blocks;
   d.spread_info = reinterpret_cast<const int4*>(h->d_spread_info);
-  d.near = h->d_near;
-  d.near_list = h->d_near_list;
-  d.near_count = h->d_near_count;
-  d.work = h->d_work;
   d.tile_box = nullptr;
-  set_near_bounds(h);
-  if (!h->swimmers.empty()) {
+  d.patch = reinterpret_cast<const int4*>(d_patch);
+  d.patch_marker = d_patch_marker;
+  d.patch_tri = reinterpret_cast<const int2*>(d_patch_tri);
+  d.patch_hinge = reinterpret_cast<const int4*>(d_patch_hinge);
+  d.patch_lane = d_patch_lane;
+  d.patch_vol = d_patch_vol;
+  d.npatch = npatch;
+  d.ntiles = h->ntiles;
+  d.nstep = (int)nstep;
+  d.step_block_box = d_step_owner;
+  d.step_box_block0 = d_step_first;
+  d.step_spread = reinterpret_cast<const int2*>(d_step_spread);
+  d.step_box = d_step_box;
+  d.step_spread_blocks = (int)step_spread.size() / 2;
+  d.folded = folded ? 1 : 0;
+  if (two_stream(h)) {
+    set_near_bounds(h);
     rc = h->hip(hipStreamCreate(&h->side), "hipStreamCreate");
     if (rc) return rc;
     h->step_events.resize(2 * kGraphChunk + 2);  // per step bulk and near, the fork, the tail
@@ -431,26 +699,13 @@ void timing_pair(lbm_handle* h, hipEvent_t* e0, hipEvent_t* e1) {
   *e1 = h->ev_pool[h->ev_used++];
 }
 
-// Enqueue `count` steps.  Without swimmers each step is one full-grid
-// stream-collide launch.  With swimmers the side stream runs the IBM chain of
-// each step -- advection of the previous step, bead statistics, nodal forces,
-// spreading -- and then the near-block launch, while the main stream streams
-// and collides every node away from the swimmers.  The last step's advection
-// closes the sequence on the main stream after a join, so the markers are
-// current whenever the sequence ends; one kernel advances the step counter.
-void enqueue_steps(lbm_handle* h, int64_t count) {
+// FP16 storage: the side stream runs the immersed-boundary chain of each step --
+// advection of the previous step, bead statistics, nodal forces, spreading --
+// and then the near-block launch, while the main stream streams and collides
+// every node away from the swimmers; in serial order (resident < 0) the chain
+// and then the full grid.
+void enqueue_two_stream(lbm_handle* h, int64_t count) {
   Dev d = h->dev;
-  if (h->swimmers.empty()) {
-    for (int64_t i = 0; i < count; ++i) {
-      d.sub = (int)i;
-      hipEvent_t e0, e1;
-      timing_pair(h, &e0, &e1);
-      launch_stream_collide(d, h->storage, kLaunchAll, h->sc_block, h->sc_blocks, h->sc_remap, 0, h->ncu, h->stream,
-                            e0, e1);
-    }
-    launch_tick(d, (int)count, h->stream);
-    return;
-  }
   if (h->sc_resident < 0) {
     // serial order: the immersed-boundary chain, then the full grid
     for (int64_t i = 0; i < count; ++i) {
@@ -510,17 +765,80 @@ void enqueue_steps(lbm_handle* h, int64_t count) {
   launch_tick(d, (int)count, h->stream);
 }
 
-// Before stepping resumes: bead regions of the current markers and the near
-// tiles under the previous step's parity, so the first step can split the
-// grid into bulk and active parts, and zeroed block counters for the
-// persistent bulk launch.  Eager, never captured.
+// Blocks of the walk that the first launch of a fused step takes: 7/16 of them,
+// a little under half, because the second launch's own work (spreading) is the
+// longer.  Measured at 1/4, 3/8, 7/16, 1/2: 128^3 in place 55.2, 53.9, 53.9,
+// 53.8 us per step, FP16 44, 42.1, 41.0, 40.1; 96^3 34.1, 33.2, 33.8, 34.5;
+// 256x128x128 110.5, 109.7, 109.7, 110.4; none or all in it cost 10 us and more
+// at 128^3.
+int step_share(const lbm_handle* h) { return h->dev.nstep / 16 * 7; }
+
+// Enqueue `count` steps on the handle's stream.  Without swimmers each step is
+// one full-grid stream-collide launch; with swimmers the two launches of the
+// fused step (step_kernels.hip), whose first advects the markers of the step
+// before; a closing launch advects those of the last step, so the markers are
+// current whenever the sequence ends, and advances the step counter.  The
+// serial order (resident < 0) runs the markers' work by itself and then the
+// full grid in one launch.
+void enqueue_steps(lbm_handle* h, int64_t count) {
+  if (two_stream(h)) return enqueue_two_stream(h, count);
+  Dev d = h->dev;
+  const bool serial = h->sc_resident < 0;
+  const int share = serial || h->swimmers.empty() ? 0 : step_share(h);
+  hipEvent_t e0, e1;
+  auto launch = [&](int mode, int nblocks, bool timed) {
+    e0 = e1 = nullptr;
+    if (timed) timing_pair(h, &e0, &e1);
+    launch_stream_collide(d, h->storage, mode, h->sc_block, nblocks, h->sc_remap, h->sc_resident, h->ncu, h->stream, e0,
+                          e1);
+  };
+  for (int64_t i = 0; i < count; ++i) {
+    d.sub = (int)i;
+    if (!h->swimmers.empty()) {
+      launch(i > 0 ? kLaunchStepA : kLaunchStepFirst, share, !serial);
+      launch(serial ? kLaunchStepSpread : kLaunchStepB, share, !serial);
+    }
+    if (serial || h->swimmers.empty()) launch(kLaunchAll, h->sc_blocks, true);
+  }
+  if (h->swimmers.empty()) {
+    launch_tick(d, (int)count, h->stream);
+  } else {
+    d.tick = (int)count;
+    launch_interp_advance(d, h->stream);
+  }
+}
+
+// No tile and no block near any step.
+int clear_near(lbm_handle* h, hipStream_t s) {
+  const Dev& d = h->dev;
+  int rc = h->hip(hipMemsetAsync(d.step_near, 0x80, sizeof(int) * 2 * (size_t)d.nstep, s), "hipMemsetAsync");
+  if (!rc) rc = h->hip(hipMemsetAsync(d.near_tile, 0x80, sizeof(int) * 2 * (size_t)d.ntiles, s), "hipMemsetAsync");
+  return rc;
+}
+
+// Before stepping resumes: the near tiles of the next step from the current
+// markers (two-stream schedule: bead regions and near blocks under the previous
+// step's parity).  Eager, never captured.
 int prologue(lbm_handle* h) {
   if (!h->need_prologue || h->swimmers.empty()) return LBM_OK;
-  int rc = h->hip(hipMemsetAsync(h->d_near, 0x80, sizeof(int) * kNearSlots * h->dev.nsc, h->stream), "hipMemsetAsync");
-  if (!rc) rc = h->hip(hipMemsetAsync(h->d_near_count, 0, sizeof(int) * 2, h->stream), "hipMemsetAsync");
-  if (!rc) rc = h->hip(hipMemsetAsync(h->d_work, 0, sizeof(int) * kWorkCounters, h->stream), "hipMemsetAsync");
+  Dev d = h->dev;
+  int rc = LBM_OK;
+  if (two_stream(h)) {
+    rc = h->hip(hipMemsetAsync(d.near, 0x80, sizeof(int) * kNearSlots * d.nsc, h->stream), "hipMemsetAsync");
+    if (!rc) rc = h->hip(hipMemsetAsync(d.near_count, 0, sizeof(int) * 2, h->stream), "hipMemsetAsync");
+    if (rc) return rc;
+    launch_bead_stats(d, -1, h->stream);
+    rc = h->hip(hipGetLastError(), "prologue launch");
+    if (!rc) h->need_prologue = false;
+    return rc;
+  }
+  rc = clear_near(h, h->stream);
   if (rc) return rc;
-  launch_bead_stats(h->dev, -1, h->stream);
+  // the regions go to a scratch state: the bead state keeps the centres the
+  // volume sums refer to
+  d.bstate_prev = h->d_bstate;
+  d.bstate = h->d_bmark;
+  launch_bead_stats(d, kMarkTiles, h->stream);
   rc = h->hip(hipGetLastError(), "prologue launch");
   if (!rc) h->need_prologue = false;
   return rc;
@@ -718,6 +1036,9 @@ int create_boxes(const lbm_box_desc* boxes, int nboxes, const lbm_opts* opts, lb
     B.omega = (float)(1.0 / d.tau);
     B.div_nx = make_divisor((uint32_t)B.nx);
     B.div_ny = make_divisor((uint32_t)B.ny);
+    B.inv[0] = 1.0 / B.nx;
+    B.inv[1] = 1.0 / B.ny;
+    B.inv[2] = 1.0 / B.nz;
     const int nb = (int)((B.n + kScBlock - 1) / kScBlock);
     block_box.insert(block_box.end(), nb, b);
     node0 += B.n;
@@ -731,24 +1052,19 @@ int create_boxes(const lbm_box_desc* boxes, int nboxes, const lbm_opts* opts, lb
   h->ntiles = tile0;
   h->out_blocks = block0;
   h->sc_table_cap = sc_cap;
-  // default stream-collide launch shape, the fastest measured on MI355X:
-  // one box, FP32 storage: one persistent 512-node workgroup per CU claiming
-  // blocks in round-robin order (128^3 swimmer step 62.3 us, 82 us at the
-  // non-persistent shape); FP16 storage: two persistent 256-node workgroups
-  // per CU; batches: non-persistent 512-node workgroups in block order
-  // (64-box ensemble 707.6 us per step against 731.5 us XCD-remapped)
-  if (nboxes > 1) {
-    h->sc_block = 512;
-    h->sc_remap = 0;
-    h->sc_resident = 0;
-  } else if (h->storage == LBM_FP16_SHIFTED) {
+  // default stream-collide launch shape, the fastest measured on MI355X.  FP16
+  // storage, one box: two persistent 256-node workgroups per CU while both
+  // population sets fit the 256 MB last-level cache (128^3 51.1 us per step,
+  // 51.8 non-persistent at 512 nodes), above it one 512-node workgroup per
+  // block (256x128x128 73.5 us, 117.1 persistent).  The other storages use it
+  // for launches without swimmers and the serial order only.
+  h->sc_block = 512;
+  h->sc_remap = 0;
+  h->sc_resident = 0;
+  if (nboxes == 1 && h->storage == LBM_FP16_SHIFTED &&
+      2 * kQ * h->pstride * (int64_t)element_bytes(h) <= kLastLevelCache) {
     h->sc_block = 256;
-    h->sc_remap = 0;
     h->sc_resident = 2;
-  } else {
-    h->sc_block = 512;
-    h->sc_remap = 0;
-    h->sc_resident = 1;
   }
 
   const size_t eb = element_bytes(h);
@@ -892,7 +1208,6 @@ int lbm_batch_swimmer_add(lbm_handle* h, int32_t box, const lbm_bead_desc beads[
   }
   Swimmer S{};
   const int sw = (int)h->swimmers.size();
-  const Box& B = h->boxes[box];
   for (int k = 0; k < 3; ++k) {
     const lbm_bead_desc& bd = beads[k];
     const Mesh M = icosphere(bd.level);
@@ -900,14 +1215,14 @@ int lbm_batch_swimmer_add(lbm_handle* h, int32_t box, const lbm_bead_desc beads[
     Bead b{};
     b.first = h->nm;
     b.nv = nv;
+    b.inv_nv = 1.0 / nv;
     b.tri0 = (int)h->tri.size() / 3;
     b.ntri = nt;
     b.box = box;
     b.swimmer = sw;
     b.slot = k;
-    b.tiles_x = reserved_tiles(bd.radius, h->width, B.nx, B.tx);
-    b.tiles_y = reserved_tiles(bd.radius, h->width, B.ny, B.ty);
-    b.tiles_z = reserved_tiles(bd.radius, h->width, B.nz, B.tz);
+    h->bead_radius.push_back(bd.radius);
+    reserve_tiles(h, b, bd.radius, 0);
     b.ks = (float)bd.kappa_s;
     b.C = (float)bd.C;
     b.kt = (float)(2.0 * bd.kappa_b / std::sqrt(3.0));
@@ -1405,7 +1720,7 @@ int lbm_set_stream_collide_launch(lbm_handle* h, int block, int xcd_remap, int r
   h->sc_resident = resident;
   rc = build_sc_tables(h);
   if (rc) return rc;
-  set_near_bounds(h);
+  if (h->uploaded && two_stream(h)) set_near_bounds(h);
   h->need_prologue = true;
   drop_graphs(h);
   return LBM_OK;
@@ -1424,14 +1739,10 @@ void snapshot_parts(lbm_handle* h, Snapshot& S) {
              {h->u, sizeof(float) * 3 * h->pstride}, {h->stamp, sizeof(int) * h->ntiles},
              {h->d_step, sizeof(int64_t)}, {h->d_overflow, sizeof(int)}};
   if (h->uploaded && h->nm > 0) {
-    const size_t nsc_max = (size_t)h->sc_table_cap;
     S.parts.push_back({h->d_pos, sizeof(double) * 3 * h->nm});
     S.parts.push_back({h->d_U, sizeof(float) * 3 * h->nm});
     S.parts.push_back({h->d_fm, sizeof(float) * 3 * h->nm});
     S.parts.push_back({h->d_bstate, sizeof(BeadState) * h->beads.size()});
-    S.parts.push_back({h->d_near, sizeof(int) * kNearSlots * nsc_max});
-    S.parts.push_back({h->d_near_list, sizeof(int) * 2 * nsc_max});
-    S.parts.push_back({h->d_near_count, sizeof(int) * 2});
   }
 }
 
@@ -1459,6 +1770,8 @@ size_t snapshot_bytes(const Snapshot& S) {
 }
 
 int element_bytes(const lbm_handle* h) { return ::element_bytes(h); }
+int step_share(const lbm_handle* h) { return ::step_share(h); }
+int clear_near(lbm_handle* h, hipStream_t s) { return ::clear_near(h, s); }
 int upload(lbm_handle* h) { return ::upload(h); }
 int prologue(lbm_handle* h) { return ::prologue(h); }
 int check_overflow(lbm_handle* h) { return ::check_overflow(h); }
