@@ -14,11 +14,8 @@
 namespace lbmib {
 
 constexpr int kGraphChunk = 32;  // steps per captured graph
-// Step graphs of every count 1..kGraphChunk: a call of n steps replays the
-// graph of n mod kGraphChunk steps once, then the chunk graph n / kGraphChunk
-// times, so a call of up to 32 steps is one graph (one fork and join of the
-// two streams; a 20-step call 59.3-60.1 against 61.5-61.8 us per step with
-// the binary split into graphs of 4 and 16 steps).
+// Steps launched directly before the chunk graph is captured (lbm_step).
+constexpr int64_t kDirectSteps = 512;
 
 template <class T>
 T* dev_alloc(size_t n, int& rc) {
@@ -108,7 +105,11 @@ struct lbm_handle {
 
   Dev dev{};
   lbmib::rt::AdjWork* adj = nullptr;  // adjoint buffers, kept between calls
-  hipGraphExec_t g_steps[lbmib::kGraphChunk + 1] = {};  // g_steps[c]: c steps
+  // g_steps[c]: c steps; every count on the two-stream schedule (one fork and
+  // join of the streams per call of up to 32 steps: a 20-step call 59.3-60.1
+  // against 61.5-61.8 us per step with a binary split), else the full chunk
+  hipGraphExec_t g_steps[lbmib::kGraphChunk + 1] = {};
+  int64_t direct_steps = 0;  // launched directly since the launches last changed
 
   bool timing = false;
   double timed_ms = 0;

@@ -537,7 +537,8 @@ __global__ __launch_bounds__(kInterpBlock) void k_interp_advance(Dev d) {
   }
 }
 
-// Bead centres of the current marker positions (observable), FP64.
+// Bead centres of the current marker positions (observable), FP64, and after
+// them the overflow flag.
 __global__ __launch_bounds__(kStatsBlock) void k_bead_centres(Dev d, double* out) {
   __shared__ double sh[kStatsBlock / 64];
   const Bead Bd = d.beads[blockIdx.x];
@@ -552,6 +553,7 @@ __global__ __launch_bounds__(kStatsBlock) void k_bead_centres(Dev d, double* out
     const double t = block_sum<kStatsBlock>(s[a], sh);
     if (threadIdx.x == 0) out[3 * blockIdx.x + a] = t / Bd.nv;
   }
+  if (blockIdx.x == 0 && threadIdx.x == 0) out[3 * d.nbeads] = (double)*d.overflow;
 }
 
 }  // namespace

@@ -17,6 +17,9 @@
 
 using namespace lbmib;
 
+// not in the host-only stand-in of the HIP runtime, where nothing is captured
+#pragma weak hipStreamIsCapturing
+
 namespace {
 
 constexpr int kReduceParts = 1024;
@@ -539,7 +542,7 @@ int upload(lbm_handle* h) {
   h->d_lane_elem = h->alloc<int>(lane_elem.size(), rc);
   h->d_lane_v = h->alloc<int>(lane_v.size(), rc);
   h->d_spread_info = h->alloc<int>(spread_info.size(), rc);
-  h->d_centres = h->alloc<double>(3 * h->beads.size(), rc);
+  h->d_centres = h->alloc<double>(3 * h->beads.size() + 1, rc);
   if (two_stream(h)) {
     // near-block buffers, sized for the smallest stream-collide block (128):
     // every box starts a new block, so the bound is the sum over the boxes of
@@ -871,6 +874,7 @@ void harvest_timing(lbm_handle* h) {
 // Drop the captured step graphs (kernel arguments or launch shapes changed);
 // the next graph-replayed call captures them again.
 void drop_graphs(lbm_handle* h) {
+  h->direct_steps = 0;
   for (auto& g : h->g_steps) {
     if (g) (void)hipGraphExecDestroy(g);
     g = nullptr;
@@ -890,6 +894,12 @@ int set_average(lbm_handle* h, double* sums, int64_t t0, int every) {
   return LBM_OK;
 }
 
+int overflow_code(lbm_handle* h, int ov) {
+  if (ov & 1) return h->fail(LBM_EOVERFLOW, "a bead outgrew its reserved tile region");
+  if (ov & 2) return h->fail(LBM_EOVERFLOW, "near-block list overflow");
+  return LBM_OK;
+}
+
 int check_overflow(lbm_handle* h) {
   if (!h->uploaded || h->swimmers.empty()) return LBM_OK;
   int ov = 0;
@@ -898,9 +908,7 @@ int check_overflow(lbm_handle* h) {
   if (rc) return rc;
   rc = h->hip(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
   if (rc) return rc;
-  if (ov & 1) return h->fail(LBM_EOVERFLOW, "a bead outgrew its reserved tile region");
-  if (ov & 2) return h->fail(LBM_EOVERFLOW, "near-block list overflow");
-  return LBM_OK;
+  return overflow_code(h, ov);
 }
 
 }  // namespace
@@ -1328,20 +1336,46 @@ int lbm_step(lbm_handle* h, int64_t n) {
     if (h->timing && h->ev_used > 256) harvest_timing(h);
     return h->hip(hipGetLastError(), "kernel launch");
   }
-  // every graph a call can replay is captured on the first call that steps,
-  // so no later call (of any step count) pays for a capture
-  for (int c = 1; c <= kGraphChunk && n > 0; ++c)
-    if (!h->g_steps[c] && (rc = capture(h, c, &h->g_steps[c]))) return rc;
-  // the remainder's graph first, then the full chunks (the smaller graph
-  // reaches the GPU sooner; the 128^3 workload: 60.05 against 60.33 us per
-  // step over 2000 steps with the remainder last)
-  const int64_t rest = n % kGraphChunk;
-  if (rest)
-    if ((rc = h->hip(hipGraphLaunch(h->g_steps[rest], h->stream), "hipGraphLaunch"))) return rc;
-  for (int64_t c = 0; c < n / kGraphChunk; ++c)
-    if ((rc = h->hip(hipGraphLaunch(h->g_steps[kGraphChunk], h->stream), "hipGraphLaunch"))) return rc;
+  if (two_stream(h)) {
+    // every graph a call can replay is captured on the first call that steps,
+    // so no later call (of any step count) pays for a capture; the remainder's
+    // graph first, then the full chunks (the smaller graph reaches the GPU
+    // sooner)
+    for (int c = 1; c <= kGraphChunk && n > 0; ++c)
+      if (!h->g_steps[c] && (rc = capture(h, c, &h->g_steps[c]))) return rc;
+    const int64_t rest = n % kGraphChunk;
+    if (rest)
+      if ((rc = h->hip(hipGraphLaunch(h->g_steps[rest], h->stream), "hipGraphLaunch"))) return rc;
+    for (int64_t c = 0; c < n / kGraphChunk; ++c)
+      if ((rc = h->hip(hipGraphLaunch(h->g_steps[kGraphChunk], h->stream), "hipGraphLaunch"))) return rc;
+    h->host_step += n;
+    return LBM_OK;
+  }
+  // On one stream a replayed graph saves host time only (128^3: 1.1 us of host
+  // and 56.2 us of GPU time per step replayed, 5.2 and 56.6 launched; a one-step
+  // call 34 us of host time replayed, 8 launched), and a captured one costs
+  // about 15 us per step once.  So the first steps after a change of the launches
+  // are launched directly, and later full chunks are replayed.
+  if (hipStreamIsCapturing) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    rc = h->hip(hipStreamIsCapturing(h->stream, &st), "hipStreamIsCapturing");
+    if (!rc && st != hipStreamCaptureStatusNone) rc = h->fail(LBM_EDEVICE, "lbm_step on a stream that is being captured");
+    if (rc) return rc;
+  }
+  for (int64_t left = n; left > 0;) {
+    if (left >= kGraphChunk && h->direct_steps >= kDirectSteps) {
+      if (!h->g_steps[kGraphChunk] && (rc = capture(h, kGraphChunk, &h->g_steps[kGraphChunk]))) return rc;
+      if ((rc = h->hip(hipGraphLaunch(h->g_steps[kGraphChunk], h->stream), "hipGraphLaunch"))) return rc;
+      left -= kGraphChunk;
+      continue;
+    }
+    const int64_t c = left % kGraphChunk ? left % kGraphChunk : kGraphChunk;
+    enqueue_steps(h, c);
+    h->direct_steps += c;
+    left -= c;
+  }
   h->host_step += n;
-  return LBM_OK;
+  return h->hip(hipGetLastError(), "kernel launch");
 }
 
 int lbm_batch_step(lbm_handle* h, int64_t n) { return lbm_step(h, n); }
@@ -1363,13 +1397,16 @@ int lbm_get_bead_centres(lbm_handle* h, double* out) {
   if (!out) return LBM_EINVAL;
   int rc = upload(h);
   if (rc) return rc;
+  // the centres and, after them, the overflow flag: one copy, one wait
+  const size_t n = 3 * h->beads.size();
+  std::vector<double> tmp(n + 1, 0.0);
   launch_bead_centres(h->dev, h->d_centres, h->stream);
-  rc = h->hip(hipMemcpyAsync(out, h->d_centres, sizeof(double) * 3 * h->beads.size(),
-                             hipMemcpyDeviceToHost, h->stream), "hipMemcpyAsync");
+  rc = h->hip(hipMemcpyAsync(tmp.data(), h->d_centres, sizeof(double) * (n + 1), hipMemcpyDeviceToHost, h->stream),
+              "hipMemcpyAsync");
+  if (!rc) rc = h->hip(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
   if (rc) return rc;
-  rc = h->hip(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
-  if (rc) return rc;
-  return check_overflow(h);
+  std::copy(tmp.begin(), tmp.end() - 1, out);
+  return overflow_code(h, (int)tmp[n]);
 }
 
 int lbm_get_swimmer_centres(lbm_handle* h, double* out) {
