@@ -96,12 +96,7 @@ __host__ __device__ inline int64_t pop_index(int q, int64_t node) {
 enum Forcing { kGuo = 0, kShanChen = 1 };
 enum Storage { kFp32 = 0, kFp16 = 1, kFp32Plain = 2, kFp32InPlace = 3 };
 
-// D3Q19 velocities c_q in the population order of the interface (0 rest,
-// 1..6 faces, 7..18 edges, opposite directions adjacent), for host code.
-constexpr int kLatticeC[kQ][3] = {{0, 0, 0},  {1, 0, 0},  {-1, 0, 0}, {0, 1, 0},   {0, -1, 0},
-                                  {0, 0, 1},  {0, 0, -1}, {1, 1, 0},  {-1, -1, 0}, {1, -1, 0},
-                                  {-1, 1, 0}, {1, 0, 1},  {-1, 0, -1}, {1, 0, -1}, {-1, 0, 1},
-                                  {0, 1, 1},  {0, -1, -1}, {0, 1, -1}, {0, -1, 1}};
+// D3Q19: the opposite of each direction (opposite directions are adjacent).
 __host__ __device__ constexpr int opposite(int q) { return q == 0 ? 0 : ((q & 1) ? q + 1 : q - 1); }
 enum ScLaunch { kLaunchAll = 0, kLaunchBulk = 1, kLaunchActive = 2, kLaunchStepFirst = 3, kLaunchStepA = 4,
                 kLaunchStepB = 5, kLaunchStepSpread = 6 };
@@ -313,6 +308,11 @@ struct Dev {
   // (rho, u) of every node, written by the moment-recording stream-collide
   // variant only (segment recompute of the adjoint)
   float4* mom;
+  // exchange of populations with the host (launch_velocity): host values
+  // [px_from, px_from + px_count) in px_buf; null: velocity and density
+  double* px_buf;
+  int64_t px_from, px_count;
+  int px_set;            // 1: px_buf -> populations, 0: populations -> px_buf
   // time average of the fluid velocity (optional): FP64 sums uavg[3][node]
   // of the u of steps avg_t0, avg_t0 + avg_every, ...; null when off
   double* uavg;
@@ -340,6 +340,8 @@ void launch_stream_collide(const Dev& d, int storage, int mode, int block, int n
 // node's (rho, u_x, u_y, u_z) to d.mom, in the step modes above.
 void launch_stream_collide_mom(const Dev& d, int mode, int nblocks, hipStream_t s);
 void launch_tick(const Dev& d, int count, hipStream_t s);
+// Node fields of the current state: velocity and density, or, with d.px_buf, the
+// exchange of populations (Dev::px_buf; nblocks is not used then).
 void launch_velocity(const Dev& d, int storage, int nblocks, float* u_out, float* rho_out,
                      hipStream_t s);
 // Mean velocity from the sums d.uavg over `count` samples (zero when count is

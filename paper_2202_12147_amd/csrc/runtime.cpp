@@ -132,32 +132,6 @@ void reserve_tiles(const lbm_handle* h, Bead& b, double radius, int margin) {
   b.tiles_z = reserved_tiles(radius, h->width, margin, B.nz, B.tz);
 }
 
-// Host layout of population deviations: box after box, each [19][n_box];
-// device index pop_index(q, node0_b + n) (256-node population blocks).
-// With the in-place storage the current state's f*_q(x) sits in slot q of
-// node x + c_q after an even number of steps (and initially), in slot
-// opposite(q) of node x after an odd number.
-template <class F>
-void for_each_population(const lbm_handle* h, F f) {
-  const bool inplace = h->storage == LBM_FP32_INPLACE, odd = (h->host_step & 1) != 0;
-  for (const Box& B : h->boxes) {
-    const int64_t hoff = kQ * B.node0;
-    for (int q = 0; q < kQ; ++q)
-      for (int64_t n = 0; n < B.n; ++n) {
-        int64_t di = pop_index(q, B.node0 + n);
-        if (inplace && odd) {
-          di = pop_index(opposite(q), B.node0 + n);
-        } else if (inplace) {
-          const int64_t x = n % B.nx, y = (n / B.nx) % B.ny, z = n / ((int64_t)B.nx * B.ny);
-          const int64_t xs = (x + kLatticeC[q][0] + B.nx) % B.nx, ys = (y + kLatticeC[q][1] + B.ny) % B.ny,
-                        zs = (z + kLatticeC[q][2] + B.nz) % B.nz;
-          di = pop_index(q, B.node0 + xs + B.nx * (ys + B.ny * zs));
-        }
-        f(hoff + q * B.n + n, di, q);
-      }
-  }
-}
-
 // Geometry signature of a handle (FNV-1a over box shapes, relaxation times,
 // forcing, storage, kernel width and markers): keys checkpoints and the tuner
 // cache.
@@ -1532,51 +1506,41 @@ int lbm_batch_get_conserved_noalloc(lbm_handle* h, int32_t box, int32_t parts, d
   return h->hip(hipGetLastError(), "conserved-sum launch");
 }
 
+// Populations between the host array (box after box, each [19][nz][ny][nx]) and
+// the device, through a device buffer of at most kExchange values.
+static int exchange_populations(lbm_handle* h, double* host, bool set) {
+  constexpr int64_t kExchange = int64_t(1) << 23;  // 64 MiB
+  const int64_t total = kQ * h->nodes;
+  Dev d = h->dev;
+  d.px_set = set ? 1 : 0;
+  const int64_t chunk = std::min(total, kExchange);
+  if (hipMalloc(reinterpret_cast<void**>(&d.px_buf), sizeof(double) * chunk) != hipSuccess)
+    return h->fail(LBM_ENOMEM, "population exchange buffer allocation failed");
+  int rc = LBM_OK;
+  for (int64_t from = 0; from < total && !rc; from += chunk) {
+    d.px_from = from;
+    d.px_count = std::min(chunk, total - from);
+    const size_t bytes = sizeof(double) * d.px_count;
+    if (set) rc = h->hip(hipMemcpyAsync(d.px_buf, host + from, bytes, hipMemcpyHostToDevice, h->stream), "hipMemcpyAsync");
+    if (!rc) launch_velocity(d, h->storage, 0, nullptr, nullptr, h->stream);
+    if (!rc) rc = h->hip(hipGetLastError(), "population exchange launch");
+    if (!rc && !set)
+      rc = h->hip(hipMemcpyAsync(host + from, d.px_buf, bytes, hipMemcpyDeviceToHost, h->stream), "hipMemcpyAsync");
+    if (!rc) rc = h->hip(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
+  }
+  (void)hipFree(d.px_buf);
+  return rc;
+}
+
 int lbm_set_populations(lbm_handle* h, const double* dev) {
   if (!h || !dev) return LBM_EINVAL;
   if (h->stepped) return h->fail(LBM_ESTATE, "populations can only be set before the first step");
-  const int cur = 0;  // step counter is 0 before stepping
-  if (h->storage == LBM_FP16_SHIFTED) {
-    std::vector<_Float16> buf(kQ * (size_t)h->pstride, (_Float16)0);
-    for_each_population(h, [&](int64_t hi, int64_t di, int) {
-      buf[di] = (_Float16)((float)dev[hi] * h->fp16_scale);
-    });
-    return h->hip(hipMemcpy(h->pop[cur], buf.data(), buf.size() * 2, hipMemcpyHostToDevice), "hipMemcpy");
-  }
-  std::vector<float> buf(kQ * (size_t)h->pstride, 0.0f);
-  if (h->storage == LBM_FP32_PLAIN)
-    for (int64_t i = 0; i < (int64_t)buf.size(); ++i) buf[i] = lattice_weight((int)((i / kPopBlock) % kQ));
-  if (h->storage == LBM_FP32_PLAIN)
-    for_each_population(h, [&](int64_t hi, int64_t di, int q) { buf[di] = (float)(lattice_weight(q) + dev[hi]); });
-  else
-    for_each_population(h, [&](int64_t hi, int64_t di, int) { buf[di] = (float)dev[hi]; });
-  return h->hip(hipMemcpy(h->pop[cur], buf.data(), buf.size() * 4, hipMemcpyHostToDevice), "hipMemcpy");
+  return exchange_populations(h, const_cast<double*>(dev), true);
 }
 
 int lbm_get_populations(lbm_handle* h, double* dev) {
   if (!h || !dev) return LBM_EINVAL;
-  int rc = h->hip(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
-  if (rc) return rc;
-  const int cur = (int)(h->host_step & 1);
-  if (h->storage == LBM_FP16_SHIFTED) {
-    std::vector<_Float16> buf(kQ * (size_t)h->pstride);
-    rc = h->hip(hipMemcpy(buf.data(), h->pop[cur], buf.size() * 2, hipMemcpyDeviceToHost), "hipMemcpy");
-    if (rc) return rc;
-    for_each_population(h, [&](int64_t hi, int64_t di, int) {
-      dev[hi] = (double)((float)buf[di] / h->fp16_scale);
-    });
-    return LBM_OK;
-  }
-  std::vector<float> buf(kQ * (size_t)h->pstride);
-  rc = h->hip(hipMemcpy(buf.data(), h->pop[cur], buf.size() * 4, hipMemcpyDeviceToHost), "hipMemcpy");
-  if (rc) return rc;
-  if (h->storage == LBM_FP32_PLAIN)
-    for_each_population(h, [&](int64_t hi, int64_t di, int q) {
-      dev[hi] = (double)buf[di] - (double)lattice_weight(q);
-    });
-  else
-    for_each_population(h, [&](int64_t hi, int64_t di, int) { dev[hi] = (double)buf[di]; });
-  return LBM_OK;
+  return exchange_populations(h, dev, false);
 }
 
 // ---- checkpoint -------------------------------------------------------------------
