@@ -14,13 +14,14 @@
 //                   the directional derivative of its volume.
 //   k_adj_tangent   32 lanes per node: the Jacobian of the Skalak, bending,
 //                   volume and spring forces (Sec. 2.2) applied to lambda_f in
-//                   dual-number FP64 arithmetic, giving lambda_r(n); lane 0 of
-//                   the first workgroup folds step n into dJ/d(A, B, alpha, k).
+//                   dual-number FP64 arithmetic, giving lambda_r(n); a
+//                   workgroup of its own folds step n into dJ/d(A, B, alpha, k).
 //
 // Every force of the model except the driving term is minus the gradient of
 // an energy, so its Jacobian is symmetric and the transposed product needed
 // by the reverse sweep equals the forward directional derivative.
 #include "adjoint.h"
+#include "ibm_device.h"
 
 #include <hip/hip_runtime.h>
 
@@ -30,11 +31,7 @@ namespace {
 
 constexpr double kW0 = 1.0 / 3.0, kW1 = 1.0 / 18.0, kW2 = 1.0 / 36.0;
 constexpr int kBlock = 256;
-
-__device__ inline int pmod(int a, int b) {
-  int r = a % b;
-  return r < 0 ? r + b : r;
-}
+constexpr int kBeadBlock = 1024;  // k_adj_bead
 
 __device__ inline double3 ld3(const double* p, int nm, int m) { return make_double3(p[m], p[nm + m], p[2 * nm + m]); }
 
@@ -239,14 +236,6 @@ __device__ inline void phi_dphi(double r, double& p, double& dp) {
   }
 }
 
-template <int NW>
-__device__ inline int stencil_base(double r) {
-  r = fmin(fmax(r, -1.0e9), 1.0e9);
-  if constexpr (NW == 3) return (int)floor(r + 0.5) - 1;
-  if constexpr (NW == 4) return (int)floor(r) - 1;
-  return (int)floor(r);
-}
-
 // With t(x) = lambda_F(x).f_m + lambda_r(n+1)_m.u(x) and Delta(x - r) =
 // phi(x1 - r1) phi(x2 - r2) phi(x3 - r3):
 //   lambda_f,m  = sum_x lambda_F(x) Delta(x - r_m)
@@ -282,8 +271,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_gather(Dev d, Adj a) {
     s[5] = -t * px * py * dz;
   }
 #pragma unroll
-  for (int k = 0; k < 6; ++k)
-    for (int sh = L / 2; sh > 0; sh >>= 1) s[k] += __shfl_xor(s[k], sh, 64);
+  for (int k = 0; k < 6; ++k) s[k] = group_reduce<L>(s[k]);
   if (m < d.nm && lane == 0) {
     const int nm = d.nm;
     a.lfm[m] = s[0];
@@ -296,34 +284,29 @@ __global__ __launch_bounds__(kBlock) void k_adj_gather(Dev d, Adj a) {
 }
 
 // ---- per-bead sums -----------------------------------------------------------------------
-__device__ inline double block_sum(double v, double* sh) {
-  for (int s = 32; s > 0; s >>= 1) v += __shfl_xor(v, s, 64);
-  const int w = threadIdx.x / 64, l = threadIdx.x % 64;
-  __syncthreads();
-  if (l == 0) sh[w] = v;
-  __syncthreads();
-  double t = 0;
-  for (int i = 0; i < kBlock / 64; ++i) t += sh[i];
-  return t;
-}
-
 // bsum[b] = (sum over the bead's nodes of lambda_f, dV[lambda_f]) with
 // dV[v] = 1/6 sum_t v0.((x1-c) x (x2-c)) + v1.((x2-c) x (x0-c)) + v2.((x0-c) x (x1-c));
 // the centre c can be any fixed point of a closed surface.
-__global__ __launch_bounds__(kBlock) void k_adj_bead(Dev d, Adj a) {
-  __shared__ double sh[kBlock / 64];
+//
+// Bound by latency: a chain of loads (triangle, its corners) on as many
+// workgroups as there are beads.  1024 lanes take the 1280 triangles of the
+// finest meshes in use in two rounds (256 lanes: five), and the four sums are
+// reduced together behind one barrier instead of one after the other: 5.5 us
+// to 4.5 us a launch beside the recompute (96^3 box, three beads).
+__global__ __launch_bounds__(kBeadBlock) void k_adj_bead(Dev d, Adj a) {
+  __shared__ double sh[kBeadBlock / 64][4];
   const int b = blockIdx.x;
   const Bead Bd = d.beads[b];
   const int nm = d.nm;
   double v[4] = {0, 0, 0, 0};
-  for (int i = threadIdx.x; i < Bd.nv; i += kBlock) {
+  for (int i = threadIdx.x; i < Bd.nv; i += kBeadBlock) {
     const int m = Bd.first + i;
     v[0] += a.lfm[m];
     v[1] += a.lfm[nm + m];
     v[2] += a.lfm[2 * nm + m];
   }
   const double* c = d.bstate[b].c;
-  for (int t = threadIdx.x; t < Bd.ntri; t += kBlock) {
+  for (int t = threadIdx.x; t < Bd.ntri; t += kBeadBlock) {
     const int tt = Bd.tri0 + t;
     const int i[3] = {d.tri[tt], d.tri[d.ntri + tt], d.tri[2 * d.ntri + tt]};
     double3 x[3], w[3];
@@ -338,9 +321,18 @@ __global__ __launch_bounds__(kBlock) void k_adj_bead(Dev d, Adj a) {
       v[3] += (w[k].x * gx + w[k].y * gy + w[k].z * gz) * (1.0 / 6.0);
     }
   }
+  const int wave = threadIdx.x / 64;
+#pragma unroll
   for (int k = 0; k < 4; ++k) {
-    const double t = block_sum(v[k], sh);
-    if (threadIdx.x == 0) a.bsum[4 * b + k] = t;
+    const double t = wave_reduce<kRedSum>(v[k]);
+    if (threadIdx.x % 64 == 0) sh[wave][k] = t;
+  }
+  __syncthreads();
+  if (threadIdx.x < 4) {
+    double t = 0;
+#pragma unroll
+    for (int i = 0; i < kBeadBlock / 64; ++i) t += sh[i][threadIdx.x];
+    a.bsum[4 * b + threadIdx.x] = t;
   }
 }
 
@@ -441,20 +433,89 @@ __device__ inline double3 bending_role_tangent(const Dev& d, const Bead& Bd, int
 // its hinges.  Lane 0 adds the volume term
 //   d f_vol = -(kv dV/V0) G - kv (V - V0)/V0 dG
 // and the spring term through the bead centres, dR_b = bsum_b / N_v.
+//
+// Bound by latency, one workgroup per compute unit or less: the FP64 dual
+// arithmetic of an element is one long dependent chain.  So nothing else may
+// follow it: the bead terms' own chain of loads and divisions comes before the
+// elements, the gradient's sines and cosines run in a workgroup of their own
+// (they were the first workgroup's tail), and the nine sums over the node's
+// lanes are register moves within rows of 16 instead of shuffles: 13.1 us to
+// 8.5 us a launch beside the recompute (96^3 box, three beads of 642 nodes),
+// 100 steps of the gradient 12.92 ms to 12.66 ms.
 constexpr int kLanes = 32;
 constexpr int kTriLanes = 8;
+// dJ/dtheta of step n, on one thread.
+__device__ inline void fold_gradient(const Dev& d, const Adj& a) {
+  // dJ/dtheta += sum over the swimmer's beads of Phi_b . d f_b/d theta, with
+  // Phi_b = bsum_b / N_v the adjoint of bead b's total (driving + spring) force
+  const Swimmer S = d.swimmers[a.swimmer];
+  double Phi[3][3];
+  for (int j = 0; j < 3; ++j)
+    for (int k = 0; k < 3; ++k) Phi[j][k] = a.bsum[4 * S.bead[j] + k] / d.beads[S.bead[j]].nv;
+  const double tn = (double)(*d.step + d.sub);
+  const double ph1 = S.omega * tn + S.phi0, ph3 = ph1 + S.alpha;
+  a.grad[0] += sin(ph1) * (Phi[0][0] - Phi[1][0]);
+  a.grad[1] += sin(ph3) * (Phi[2][0] - Phi[1][0]);
+  a.grad[2] += S.B * cos(ph3) * (Phi[2][0] - Phi[1][0]);
+  const double* R1 = d.bstate[S.bead[1]].c;
+  double gk = 0;
+  for (int sp = 0; sp < 2; ++sp) {
+    const int outer = sp == 0 ? 0 : 2;
+    const double* Ro = d.bstate[S.bead[outer]].c;
+    const double dx = Ro[0] - R1[0], dy = Ro[1] - R1[1], dz = Ro[2] - R1[2];
+    const double len = sqrt(dx * dx + dy * dy + dz * dz);
+    const double c = -(len - S.L0[sp]) / len;  // d f_spring / d k = c (R_o - R_2)
+    gk += c * (dx * (Phi[outer][0] - Phi[1][0]) + dy * (Phi[outer][1] - Phi[1][1]) + dz * (Phi[outer][2] - Phi[1][2]));
+  }
+  a.grad[3] += gk;
+}
+
 __global__ __launch_bounds__(kBlock) void k_adj_tangent(Dev d, Adj a) {
+  // the last workgroup folds the gradient (sines and cosines of the driving
+  // phase: longer than a node's own work)
+  if (blockIdx.x == gridDim.x - 1) {
+    if (threadIdx.x == 0) fold_gradient(d, a);
+    return;
+  }
   const int gid = blockIdx.x * kBlock + threadIdx.x;
   const int m = gid / kLanes, lane = gid % kLanes;
   const int nm = d.nm;
   double s[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};  // force tangent, G, dG
-  int b = 0;
+  // the bead terms, in every lane of the node's group: their chain of loads
+  // (bead, swimmer, the beads of the swimmer) runs beside the elements' own
+  double dpref = 0, pref = 0, fs[3] = {0, 0, 0};
   if (m < nm) {
-    b = d.marker_bead[m];
+    const int b = d.marker_bead[m];
     const int e = d.lane_elem[gid];
     const int4 v = d.lane_v[gid];
+    const Bead Bd = d.beads[b];
+    const double kv = (double)Bd.kv;
+    const double kV = kv / Bd.V0;
+    pref = kV * (d.bstate[b].V - Bd.V0);
+    dpref = kV * a.bsum[4 * b + 3];
+    if (Bd.swimmer >= 0) {
+      const Swimmer S = d.swimmers[Bd.swimmer];
+      const double* R1 = d.bstate[S.bead[1]].c;
+      const Bead B1 = d.beads[S.bead[1]];
+      for (int sp = 0; sp < 2; ++sp) {
+        const int outer = sp == 0 ? 0 : 2;
+        if (Bd.slot != outer && Bd.slot != 1) continue;
+        const Bead Bo = d.beads[S.bead[outer]];
+        const double* Ro = d.bstate[S.bead[outer]].c;
+        double dd[3], dD[3];
+        for (int k = 0; k < 3; ++k) {
+          dd[k] = Ro[k] - R1[k];
+          dD[k] = a.bsum[4 * S.bead[outer] + k] * Bo.inv_nv - a.bsum[4 * S.bead[1] + k] * B1.inv_nv;
+        }
+        const double len = sqrt(dd[0] * dd[0] + dd[1] * dd[1] + dd[2] * dd[2]);
+        const double il = 1.0 / len;
+        const double dlen = (dd[0] * dD[0] + dd[1] * dD[1] + dd[2] * dD[2]) * il;
+        const double ks = (Bd.slot == outer ? -S.k[sp] : S.k[sp]) * Bd.inv_nv * il;
+        for (int k = 0; k < 3; ++k)
+          fs[k] += ks * (dlen * dd[k] + (len - S.L0[sp]) * (dD[k] - dd[k] * dlen * il));
+      }
+    }
     if (e >= 0) {
-      const Bead Bd = d.beads[b];
       if (lane < kTriLanes) {
         const int t = e / 3, corner = e % 3;
         const D3 p[3] = {load_d3(d, a, v.x), load_d3(d, a, v.y), load_d3(d, a, v.z)};
@@ -494,66 +555,15 @@ __global__ __launch_bounds__(kBlock) void k_adj_tangent(Dev d, Adj a) {
     }
   }
 #pragma unroll
-  for (int k = 0; k < 9; ++k)
-    for (int sh = kLanes / 2; sh > 0; sh >>= 1) s[k] += __shfl_xor(s[k], sh, 64);
+  for (int k = 0; k < 9; ++k) s[k] = group_reduce<kLanes>(s[k]);
   if (m < nm && lane == 0) {
-    const Bead Bd = d.beads[b];
-    const double V = d.bstate[b].V, kv = (double)Bd.kv;
-    const double pref = kv * (V - Bd.V0) / Bd.V0, dpref = kv * a.bsum[4 * b + 3] / Bd.V0;
     double t[3];
-    for (int k = 0; k < 3; ++k) t[k] = s[k] - dpref * s[3 + k] - pref * s[6 + k];
-    if (Bd.swimmer >= 0) {
-      const Swimmer S = d.swimmers[Bd.swimmer];
-      const double* R1 = d.bstate[S.bead[1]].c;
-      const Bead B1 = d.beads[S.bead[1]];
-      for (int sp = 0; sp < 2; ++sp) {
-        const int outer = sp == 0 ? 0 : 2;
-        if (Bd.slot != outer && Bd.slot != 1) continue;
-        const Bead Bo = d.beads[S.bead[outer]];
-        const double* Ro = d.bstate[S.bead[outer]].c;
-        double dd[3], dD[3];
-        for (int k = 0; k < 3; ++k) {
-          dd[k] = Ro[k] - R1[k];
-          dD[k] = a.bsum[4 * S.bead[outer] + k] / Bo.nv - a.bsum[4 * S.bead[1] + k] / B1.nv;
-        }
-        const double len = sqrt(dd[0] * dd[0] + dd[1] * dd[1] + dd[2] * dd[2]);
-        const double dlen = (dd[0] * dD[0] + dd[1] * dD[1] + dd[2] * dD[2]) / len;
-        const double sign = Bd.slot == outer ? 1.0 : -1.0;
-        for (int k = 0; k < 3; ++k) {
-          const double dfs = -S.k[sp] * (dlen * dd[k] / len + (len - S.L0[sp]) * (dD[k] / len - dd[k] * dlen / (len * len)));
-          t[k] += sign * dfs / Bd.nv;
-        }
-      }
-    }
+    for (int k = 0; k < 3; ++k) t[k] = s[k] - dpref * s[3 + k] - pref * s[6 + k] + fs[k];
     for (int k = 0; k < 3; ++k) {
       const double l = a.ltmp[k * nm + m] + t[k];
       a.lr[k * nm + m] = l;
       a.lr32[k * nm + m] = (float)l;
     }
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    // dJ/dtheta += sum over the swimmer's beads of Phi_b . d f_b/d theta, with
-    // Phi_b = bsum_b / N_v the adjoint of bead b's total (driving + spring) force
-    const Swimmer S = d.swimmers[a.swimmer];
-    double Phi[3][3];
-    for (int j = 0; j < 3; ++j)
-      for (int k = 0; k < 3; ++k) Phi[j][k] = a.bsum[4 * S.bead[j] + k] / d.beads[S.bead[j]].nv;
-    const double tn = (double)(*d.step + d.sub);
-    const double ph1 = S.omega * tn + S.phi0, ph3 = ph1 + S.alpha;
-    a.grad[0] += sin(ph1) * (Phi[0][0] - Phi[1][0]);
-    a.grad[1] += sin(ph3) * (Phi[2][0] - Phi[1][0]);
-    a.grad[2] += S.B * cos(ph3) * (Phi[2][0] - Phi[1][0]);
-    const double* R1 = d.bstate[S.bead[1]].c;
-    double gk = 0;
-    for (int sp = 0; sp < 2; ++sp) {
-      const int outer = sp == 0 ? 0 : 2;
-      const double* Ro = d.bstate[S.bead[outer]].c;
-      const double dx = Ro[0] - R1[0], dy = Ro[1] - R1[1], dz = Ro[2] - R1[2];
-      const double len = sqrt(dx * dx + dy * dy + dz * dz);
-      const double c = -(len - S.L0[sp]) / len;  // d f_spring / d k = c (R_o - R_2)
-      gk += c * (dx * (Phi[outer][0] - Phi[1][0]) + dy * (Phi[outer][1] - Phi[1][1]) + dz * (Phi[outer][2] - Phi[1][2]));
-    }
-    a.grad[3] += gk;
   }
 }
 
@@ -601,12 +611,12 @@ void launch_adj_gather(const Dev& d, const Adj& a, hipStream_t s) {
 }
 
 void launch_adj_bead(const Dev& d, const Adj& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_adj_bead, dim3(d.nbeads), dim3(kBlock), 0, s, d, a);
+  hipLaunchKernelGGL(k_adj_bead, dim3(d.nbeads), dim3(kBeadBlock), 0, s, d, a);
 }
 
 void launch_adj_tangent(const Dev& d, const Adj& a, hipStream_t s) {
   const int blocks = (int)(((int64_t)d.nm * kLanes + kBlock - 1) / kBlock);
-  hipLaunchKernelGGL(k_adj_tangent, dim3(blocks), dim3(kBlock), 0, s, d, a);
+  hipLaunchKernelGGL(k_adj_tangent, dim3(blocks + 1), dim3(kBlock), 0, s, d, a);
 }
 
 void launch_set_step(int64_t* step, int64_t value, hipStream_t s) {
