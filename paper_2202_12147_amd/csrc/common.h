@@ -75,7 +75,9 @@ constexpr int kSlabLayers = 2;       // z layers of a spreading slab
 constexpr int kSlabParts = kTile / kSlabLayers;
 constexpr int kNearMargin = 2;
 constexpr int kFoldBeads = 64;
-constexpr int kSlabWorkers = 64;  // spreading workgroups per bead at most
+// Spreading workgroups per bead at most, and at least where their number is
+// limited to kSlabGrid (two per compute unit) over all beads.
+constexpr int kSlabWorkers = 64, kSlabWorkersMin = 8, kSlabGrid = 512;
 constexpr int kFoldPatches = 256;
 constexpr int kPopBlock = 256; // nodes per population block (a power of two: shifts and masks)
 // mark_offset of launch_bead_stats / launch_stats_forces that leaves the near

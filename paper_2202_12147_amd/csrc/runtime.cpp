@@ -202,12 +202,15 @@ void set_near_bounds(lbm_handle* h) {
 //    its earlier values.
 //  - batches of many beads: there the number of the markers' workgroups decides,
 //    not their latency, and the fused step's patches advance their border nodes
-//    twice (32 boxes, 11.8 M nodes: 441 us per step against 522 fused; 24 boxes,
-//    72 beads: 201 and 199; 16 boxes: 254 and 237).
-constexpr int kFusedBatchBeads = 64;
+//    twice.  Up to kWriteThroughBytes of populations: 24 boxes, 1.7 M nodes 127 us
+//    per step against 106 fused; 32 boxes, 5.6 M 297 and 271; 40 boxes, 6.7 M 358
+//    and 344; 60 boxes, 6.6 M 259 and 291.  Beyond: 16 boxes 254 and 237; 32 boxes,
+//    11.8 M 441 and 522; 40 boxes, 7.5 M 323 and 361.
+constexpr int kFusedBatchBeads = 64, kFusedBatchBeadsSmall = 128;
 bool two_stream(const lbm_handle* h) {
   if (h->swimmers.empty()) return false;
-  return h->storage == LBM_FP16_SHIFTED || (h->boxes.size() > 1 && h->beads.size() > (size_t)kFusedBatchBeads);
+  const int most = h->dev.small_pops ? kFusedBatchBeadsSmall : kFusedBatchBeads;
+  return h->storage == LBM_FP16_SHIFTED || (h->boxes.size() > 1 && h->beads.size() > (size_t)most);
 }
 
 // ---- surface patches (Dev::patch) ------------------------------------------------
@@ -464,6 +467,18 @@ int upload(lbm_handle* h) {
   std::vector<StepBox> step_box(h->boxes.size());
   bool folded = false;
   int64_t slabs = 0;
+  // Spreading workgroups per bead.  Each first folds its box's bead terms and then
+  // walks its share of the slabs.  Few beads leave the chip idle, so a slab or two
+  // each (64 per bead); many fill it several times over and repeat the folding, so
+  // there the whole handle gets kSlabGrid.  32^3 to 80^3 boxes, 64 per bead against
+  // kSlabGrid in all, us per step: 3 boxes 24 and 24 (8 per bead: 42), 8 boxes 44.7
+  // and 40.5, 16 boxes 148 and 133, 21 boxes 209 and 188.  Markers over several
+  // chunks make a slab long (three 1280-triangle beads, 192 workgroups 62, 96 65.5),
+  // and beyond kWriteThroughBytes of populations the blocks are slow beside a
+  // few long-running workgroups (14 boxes, 7.4 M nodes: 290 and 302).
+  const int few = h->dev.small_pops && !h->beads.empty()
+                      ? std::min(kSlabWorkers, std::max(kSlabWorkersMin, kSlabGrid / (int)h->beads.size()))
+                      : 0;
   for (size_t i = 0; fused && i < h->boxes.size(); ++i) {
     const Box& B = h->boxes[i];
     StepBox& sx = step_box[i];
@@ -483,7 +498,8 @@ int upload(lbm_handle* h) {
     for (int b = B.bead0; b < B.bead0 + B.nbeads; ++b)
       mine += (int64_t)h->beads[b].tiles_x * h->beads[b].tiles_y * h->beads[b].tiles_z * kSlabParts;
     slabs += mine;
-    sx.workers = (int)std::min<int64_t>(mine, (int64_t)kSlabWorkers * B.nbeads);
+    const bool one_chunk = sx.m_end - sx.m0 <= kStepBlock;
+    sx.workers = (int)std::min<int64_t>(mine, (int64_t)(few > 0 && one_chunk ? few : kSlabWorkers) * B.nbeads);
     for (int c = 0; c < sx.workers; ++c) {
       const int e[2] = {(int)i, c};
       step_spread.insert(step_spread.end(), e, e + 2);

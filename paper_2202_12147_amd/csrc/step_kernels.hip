@@ -20,6 +20,12 @@
 // units, and there is no second stream, whose cross-stream graph edges cost
 // about 5 us of queue time each.
 //
+// Per step, against the chain in five kernels on a second stream beside one
+// launch of the other blocks (us): 32^3 36.0 to 19.5, 64^3 36.3 to 26.5, 96^3
+// 45.9 to 33.6, 128^3 in place 56.9 to 52.9 and with two sets 58.4 to 55.4,
+// 256x128x128 127.5 to 109.3, 1024x256x256 2152 to 1751.  At 128^3 in place
+// k_step_a takes 22.6 us and k_step_b 29.4 (13.0 and 13.1 without blocks).
+//
 // What a launch reads was written by an earlier launch, except for data of the
 // same workgroup: k_step_a reads the positions in d.pos and writes d.pos_new;
 // k_step_b reads d.pos_new and its bead workgroups copy it to d.pos.  The near

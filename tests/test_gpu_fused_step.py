@@ -53,7 +53,7 @@ def test_fine_meshes(width):
 
 
 def test_large_batch_matches_fused_boxes():
-    # 22 boxes (66 beads) run the two-stream schedule, each alone the fused step
+    # 22 boxes (66 beads) share a bounded number of spreading workgroups
     ens = wl.ensemble(seed=11, nboxes=22)
     for b in ens["boxes"]:
         b["shape"] = tuple(max(33, s // 2 + 1) for s in b["shape"])
