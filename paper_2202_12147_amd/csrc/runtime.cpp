@@ -132,6 +132,64 @@ void reserve_tiles(const lbm_handle* h, Bead& b, double radius, int margin) {
   b.tiles_z = reserved_tiles(radius, h->width, margin, B.nz, B.tz);
 }
 
+// D3Q19 velocities, opposite directions adjacent.
+constexpr int kLatticeC[kQ][3] = {{0, 0, 0},  {1, 0, 0},  {-1, 0, 0}, {0, 1, 0},   {0, -1, 0},
+                                  {0, 0, 1},  {0, 0, -1}, {1, 1, 0},  {-1, -1, 0}, {1, -1, 0},
+                                  {-1, 1, 0}, {1, 0, 1},  {-1, 0, -1}, {1, 0, -1}, {-1, 0, 1},
+                                  {0, 1, 1},  {0, -1, -1}, {0, 1, -1}, {0, -1, 1}};
+
+// Host layout of population deviations: box after box, each [19][n_box];
+// device index pop_index(q, node0_b + n) (256-node population blocks).
+// With the in-place storage the current state's f*_q(x) sits in slot q of
+// node x + c_q after an even number of steps (and initially), in slot
+// opposite(q) of node x after an odd number.
+template <class F>
+void for_each_population(const lbm_handle* h, F f) {
+  const bool inplace = h->storage == LBM_FP32_INPLACE, odd = (h->host_step & 1) != 0;
+  for (const Box& B : h->boxes) {
+    const int64_t hoff = kQ * B.node0;
+    for (int q = 0; q < kQ; ++q)
+      for (int64_t n = 0; n < B.n; ++n) {
+        int64_t di = pop_index(q, B.node0 + n);
+        if (inplace && odd) {
+          di = pop_index(opposite(q), B.node0 + n);
+        } else if (inplace) {
+          const int64_t x = n % B.nx, y = (n / B.nx) % B.ny, z = n / ((int64_t)B.nx * B.ny);
+          const int64_t xs = (x + kLatticeC[q][0] + B.nx) % B.nx, ys = (y + kLatticeC[q][1] + B.ny) % B.ny,
+                        zs = (z + kLatticeC[q][2] + B.nz) % B.nz;
+          di = pop_index(q, B.node0 + xs + B.nx * (ys + B.ny * zs));
+        }
+        f(hoff + q * B.n + n, di, q);
+      }
+  }
+}
+
+// Populations between the host array (box after box, each [19][nz][ny][nx]) and
+// the device, converted on the host.
+template <class T>
+int host_populations(lbm_handle* h, double* host, bool set) {
+  std::vector<T> buf(kQ * (size_t)h->pstride, (T)0);
+  void* const pop = h->pop[set ? 0 : h->host_step & 1];
+  const size_t bytes = buf.size() * sizeof(T);
+  const float scale = h->storage == LBM_FP16_SHIFTED ? h->fp16_scale : 1.0f;
+  const bool plain = h->storage == LBM_FP32_PLAIN;
+  if (set) {
+    if (plain)
+      for (int64_t i = 0; i < (int64_t)buf.size(); ++i) buf[i] = (T)lattice_weight((int)((i / kPopBlock) % kQ));
+    for_each_population(h, [&](int64_t hi, int64_t di, int q) {
+      buf[di] = (T)((plain ? (float)(lattice_weight(q) + host[hi]) : (float)host[hi]) * scale);
+    });
+    return h->hip(hipMemcpy(pop, buf.data(), bytes, hipMemcpyHostToDevice), "hipMemcpy");
+  }
+  int rc = h->hip(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
+  if (!rc) rc = h->hip(hipMemcpy(buf.data(), pop, bytes, hipMemcpyDeviceToHost), "hipMemcpy");
+  if (rc) return rc;
+  for_each_population(h, [&](int64_t hi, int64_t di, int q) {
+    host[hi] = (double)((float)buf[di] / scale) - (double)(plain ? lattice_weight(q) : 0.0f);
+  });
+  return LBM_OK;
+}
+
 // Geometry signature of a handle (FNV-1a over box shapes, relaxation times,
 // forcing, storage, kernel width and markers): keys checkpoints and the tuner
 // cache.
@@ -1523,15 +1581,24 @@ int lbm_batch_get_conserved_noalloc(lbm_handle* h, int32_t box, int32_t parts, d
 }
 
 // Populations between the host array (box after box, each [19][nz][ny][nx]) and
-// the device, through a device buffer of at most kExchange values.
+// the device, through a device buffer of at most kExchange values (fewer, down
+// to kExchangeMin, where device memory is short).
 static int exchange_populations(lbm_handle* h, double* host, bool set) {
-  constexpr int64_t kExchange = int64_t(1) << 23;  // 64 MiB
+  constexpr int64_t kExchange = int64_t(1) << 23, kExchangeMin = int64_t(1) << 16;  // 64 MiB, 512 KiB
+  // Up to kHostExchange values the host converts (the buffer, the launch and their waits cost as much).
+  constexpr int64_t kHostExchange = int64_t(1) << 17;
   const int64_t total = kQ * h->nodes;
+  if (total <= kHostExchange)
+    return h->storage == LBM_FP16_SHIFTED ? host_populations<_Float16>(h, host, set)
+                                          : host_populations<float>(h, host, set);
   Dev d = h->dev;
   d.px_set = set ? 1 : 0;
-  const int64_t chunk = std::min(total, kExchange);
-  if (hipMalloc(reinterpret_cast<void**>(&d.px_buf), sizeof(double) * chunk) != hipSuccess)
-    return h->fail(LBM_ENOMEM, "population exchange buffer allocation failed");
+  int64_t chunk = std::min(total, kExchange);
+  while (hipMalloc(reinterpret_cast<void**>(&d.px_buf), sizeof(double) * chunk) != hipSuccess) {
+    (void)hipGetLastError();
+    if (chunk <= kExchangeMin) return h->fail(LBM_ENOMEM, "population exchange buffer allocation failed");
+    chunk /= 2;
+  }
   int rc = LBM_OK;
   for (int64_t from = 0; from < total && !rc; from += chunk) {
     d.px_from = from;
