@@ -20,22 +20,15 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_HBM_GBS = 8000.0
-# stream-collide launch shapes (block, XCD remap, resident workgroups per CU),
-# measured best for these workloads on MI355X by explicit sweeps: the 128^3
-# FP32 step with one resident 512-node workgroup per CU claiming blocks in
-# round-robin order (62.3 us against 63.0 us for two of 256 nodes, 64.9 us
-# remapped); FP16 (static persistent walk) at two of 256 nodes; the batch
-# and the 1024x256x256 box non-persistent with the XCD remap (batch 724.7
-# against 729.5 us in block order, 760-940 us persistent; box 1.842 ms
-# against 1.849 ms in block order and 1.869 ms at block 256).  The batch
-# section itself runs the launch tuner (lbmib.tune_launch) and times the
-# shape it picks (block order, 707.6 us against 731.5 us remapped, in the
-# tuner's first run); BATCH_LAUNCH is that shape, which the parity test of
-# the full ensemble uses.  The paper-box section tunes too.
+# stream-collide launch shapes (block, XCD remap, resident) of the workloads.
+# Single FP32 boxes with swimmers run the fused step, whatever the shape, for
+# resident >= 0; the shape matters with FP16 storage and for large batches.  The
+# batch section runs the launch tuner (lbmib.tune_launch) and times the shape it
+# picks; BATCH_LAUNCH is the shape the parity test of the full ensemble uses.
 MAIN_LAUNCH = (512, False, 1)
 # The 128^3 workload's populations: FP32 deviations in one set updated in
 # place (LBM_FP32_INPLACE; 159 MB instead of two sets of 319 MB, which the
-# 256 MB last-level cache holds: step 56.6 against 57.6-58.5 us with two sets,
+# 256 MB last-level cache holds: step 52.9 against 55.5 us with two sets,
 # bit-identical results)
 MAIN_STORAGE = 3
 FP16_LAUNCH = (256, False, 2)
@@ -43,7 +36,8 @@ BATCH_LAUNCH = (512, False, 0)
 BOX_LAUNCH = (512, True, 0)
 KERNEL_LAUNCH = (256, False, -1)  # serial order: full-grid launch for the roofline
 PMC_PROFILE = os.path.join(ROOT, "profiles", "stream_collide_128cubed_pmc.txt")
-KERNEL_SOURCE = os.path.join(ROOT, "paper_2202_12147_amd", "csrc", "lattice_kernels.hip")
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2202_12147_amd", "csrc", f)
+                  for f in ("lattice_device.h", "lattice_kernels.hip")]
 
 
 def measured_traffic():
@@ -53,10 +47,9 @@ def measured_traffic():
     try:
         fields = dict(line.split(": ", 1) for line in open(PMC_PROFILE).read().splitlines()
                       if line and not line.startswith("#"))
-        src = open(KERNEL_SOURCE).read()
+        dev = "".join(src[:src.index("}  // namespace")] for src in (open(f).read() for f in KERNEL_SOURCES))
     except OSError:
         return None
-    dev = src[:src.index("}  // namespace")]
     if hashlib.sha256(dev.encode()).hexdigest() != fields.get("kernel_source_sha256", "").strip():
         return None
     return int(fields["traffic_bytes_per_launch"])
@@ -219,7 +212,8 @@ def adjoint_section(lbmib, wl, use_graphs=True):
     lbm_adjoint (checkpointed forward + segment recompute + reverse sweep)
     against the plain forward run of the same steps.  use_graphs=False
     launches every kernel directly (counter collection: the profiler's
-    counter mode does not survive replays of the two-stream graphs)."""
+    counter mode does not survive replays of the reverse sweep's two-stream
+    graphs)."""
     case = wl.adjoint_case(reduced=False)
     T, K = case["steps"], case["checkpoint"]
     nodes = case["shape"][0] * case["shape"][1] * case["shape"][2]
@@ -432,7 +426,7 @@ def main():
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     lat.step(args.steps)
-    torch.cuda.synchronize()  # the whole device: the library's side stream included
+    torch.cuda.synchronize()
     dt = time.perf_counter() - t0
     lat.sync()  # then the overflow check (a bead outgrowing its tiles), outside the timed steps
     ms_per_step = dt / args.steps * 1e3
