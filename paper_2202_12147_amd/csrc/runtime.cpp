@@ -620,6 +620,8 @@ int upload(lbm_handle* h) {
   h->dev.step_near = h->alloc<int>(2 * nstep, rc);
   h->d_bmark = h->alloc<BeadState>(h->beads.size(), rc);
   if (rc != LBM_OK) return h->fail(rc, "device allocation for markers failed");
+  // no near tiles until a step's are marked
+  rc = h->hip(hipMemset(h->dev.near_range, 0, sizeof(NearRange) * 2 * h->beads.size()), "hipMemset");
   put(d_patch, P.head.data(), sizeof(int) * P.head.size());
   put(d_patch_marker, P.marker.data(), sizeof(int) * P.marker.size());
   put(d_patch_tri, P.tri.data(), sizeof(int) * P.tri.size());
@@ -867,20 +869,31 @@ int clear_near(lbm_handle* h, hipStream_t s) {
   return rc;
 }
 
+// Whether the handle's stream is under capture by the caller.
+int capturing(lbm_handle* h, bool* out) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  const int rc = hipStreamIsCapturing ? h->hip(hipStreamIsCapturing(h->stream, &st), "hipStreamIsCapturing") : LBM_OK;
+  *out = st != hipStreamCaptureStatusNone;
+  return rc;
+}
+
 // Before stepping resumes: the near tiles of the next step from the current
 // markers (two-stream schedule: bead regions and near blocks under the previous
-// step's parity).  Eager, never captured.
+// step's parity).  In no graph of the library's own; recorded into a caller's
+// graph (a handle without graphs), the marks are still to be made.
 int prologue(lbm_handle* h) {
   if (!h->need_prologue || h->swimmers.empty()) return LBM_OK;
   Dev d = h->dev;
-  int rc = LBM_OK;
+  bool recording = false;
+  int rc = capturing(h, &recording);
+  if (rc) return rc;
   if (two_stream(h)) {
     rc = h->hip(hipMemsetAsync(d.near, 0x80, sizeof(int) * kNearSlots * d.nsc, h->stream), "hipMemsetAsync");
     if (!rc) rc = h->hip(hipMemsetAsync(d.near_count, 0, sizeof(int) * 2, h->stream), "hipMemsetAsync");
     if (rc) return rc;
     launch_bead_stats(d, -1, h->stream);
     rc = h->hip(hipGetLastError(), "prologue launch");
-    if (!rc) h->need_prologue = false;
+    if (!rc) h->need_prologue = recording;
     return rc;
   }
   rc = clear_near(h, h->stream);
@@ -891,7 +904,7 @@ int prologue(lbm_handle* h) {
   d.bstate = h->d_bmark;
   launch_bead_stats(d, kMarkTiles, h->stream);
   rc = h->hip(hipGetLastError(), "prologue launch");
-  if (!rc) h->need_prologue = false;
+  if (!rc) h->need_prologue = recording;
   return rc;
 }
 
@@ -1373,9 +1386,12 @@ int lbm_set_body_force(lbm_handle* h, const double g[3]) {
 
 int lbm_step(lbm_handle* h, int64_t n) {
   if (!h || n < 0) return LBM_EINVAL;
-  int rc = upload(h);
-  if (rc) return rc;
-  rc = prologue(h);
+  // before anything is recorded or marked as done
+  bool recording = false;
+  int rc = h->use_graphs && !h->timing ? capturing(h, &recording) : LBM_OK;
+  if (!rc && recording) rc = h->fail(LBM_EDEVICE, "lbm_step on a stream that is being captured");
+  if (!rc) rc = upload(h);
+  if (!rc) rc = prologue(h);
   if (rc) return rc;
   h->stepped = true;
   if (h->timing || !h->use_graphs) {
@@ -1404,12 +1420,6 @@ int lbm_step(lbm_handle* h, int64_t n) {
   // call 34 us of host time replayed, 8 launched), and a captured one costs
   // about 15 us per step once.  So the first steps after a change of the launches
   // are launched directly, and later full chunks are replayed.
-  if (hipStreamIsCapturing) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    rc = h->hip(hipStreamIsCapturing(h->stream, &st), "hipStreamIsCapturing");
-    if (!rc && st != hipStreamCaptureStatusNone) rc = h->fail(LBM_EDEVICE, "lbm_step on a stream that is being captured");
-    if (rc) return rc;
-  }
   for (int64_t left = n; left > 0;) {
     if (left >= kGraphChunk && h->direct_steps >= kDirectSteps) {
       if (!h->g_steps[kGraphChunk] && (rc = capture(h, kGraphChunk, &h->g_steps[kGraphChunk]))) return rc;

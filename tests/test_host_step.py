@@ -1,0 +1,93 @@
+"""lbm_step's bookkeeping on the host, against the HIP stand-in of
+tests/hoststub (no GPU, no kernel runs): a call that is refused because the
+caller captures the stream leaves nothing marked as done."""
+import ctypes as C
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CLANG = "/opt/rocm/llvm/bin/clang++"
+WRAPPED = ["hipStreamBeginCapture", "hipStreamEndCapture", "hipGraphInstantiate", "hipGraphLaunch",
+           "_ZN5lbmib17launch_bead_statsERKNS_3DevEiP12ihipStream_t",
+           "_ZN5lbmib21launch_interp_advanceERKNS_3DevEP12ihipStream_t"]
+
+pytestmark = pytest.mark.skipif(not os.path.exists(CLANG), reason="needs the ROCm clang++")
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("stub") / "libhoststep.so")
+    csrc = os.path.join(ROOT, "paper_2202_12147_amd", "csrc")
+    here = os.path.join(ROOT, "tests", "hoststub")
+    subprocess.run([CLANG, "-x", "c++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-D__HIP_MEMORY_SCOPE_SYSTEM=5",
+                    "-I/opt/rocm/include", "-I" + os.path.join(ROOT, "include"), "-O1", "-fPIC", "-shared",
+                    os.path.join(csrc, "runtime.cpp"), os.path.join(csrc, "adjoint.cpp"),
+                    os.path.join(here, "hip_stub.cpp"), os.path.join(here, "step_control.cpp"), "-o", lib]
+                   + ["-Wl,--wrap=" + w for w in WRAPPED], check=True)
+    return lib
+
+
+def _run(stub, body):
+    """`body` in a process of its own (the stand-in's state is global), with
+    `lat` a 32^3 swimmer handle, control() and records() in scope."""
+    prelude = f"""
+import ctypes as C, sys
+sys.path.insert(0, {ROOT!r})
+from paper_2202_12147_amd import lbmib, workloads as wl
+lib = C.CDLL({stub!r})
+lbmib._lib = lbmib.bind(lib)
+def control(capturing=0, fail_instantiate=0, fail_launch=-1):
+    lib.control(capturing, fail_instantiate, fail_launch)
+def records():
+    out = (C.c_long * 4)()
+    lib.records(out)
+    return list(out)
+def refused(f, *a):
+    try:
+        f(*a)
+    except lbmib.LbmError as e:
+        assert e.code == -3, e
+    else:
+        raise AssertionError("the call was not refused")
+case = wl.small_case()
+def handle(**kw):
+    return lbmib.from_workload(case, **kw)
+"""
+    r = subprocess.run([sys.executable, "-c", prelude + body], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("storage", [0, 1])  # the fused and the two-stream schedule
+def test_refused_under_capture_leaves_the_marks_to_be_made(stub, storage):
+    _run(stub, f"""
+lat = handle(storage={storage})
+control(capturing=1)
+refused(lat.step, 3)
+assert records()[0] == 0 and lat.time == 0
+lat.set_populations([0.0] * (19 * 32 ** 3))    # nothing was stepped
+control()
+lat.step(3)
+assert records()[0] == 1 and lat.time == 3
+""")
+
+
+def test_recorded_marks_are_made_again(stub):
+    # a handle without graphs may be recorded by the caller; its marks are then
+    # made by the caller's graph only, so the next direct call makes its own
+    _run(stub, """
+lat = handle(use_graphs=False)
+lat.step(0)
+assert records()[0] == 1
+lat.set_stream_collide_launch(512, False, 0)   # marks to be made anew
+control(capturing=1)
+lat.step(2)
+assert records()[0] == 2
+control()
+lat.step(2)
+assert records()[0] == 3
+lat.step(2)
+assert records()[0] == 3
+""")
