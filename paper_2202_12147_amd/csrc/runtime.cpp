@@ -1407,12 +1407,12 @@ int lbm_step(lbm_handle* h, int64_t n) {
     // sooner)
     for (int c = 1; c <= kGraphChunk && n > 0; ++c)
       if (!h->g_steps[c] && (rc = capture(h, c, &h->g_steps[c]))) return rc;
-    const int64_t rest = n % kGraphChunk;
-    if (rest)
-      if ((rc = h->hip(hipGraphLaunch(h->g_steps[rest], h->stream), "hipGraphLaunch"))) return rc;
-    for (int64_t c = 0; c < n / kGraphChunk; ++c)
-      if ((rc = h->hip(hipGraphLaunch(h->g_steps[kGraphChunk], h->stream), "hipGraphLaunch"))) return rc;
-    h->host_step += n;
+    for (int64_t left = n; left > 0;) {
+      const int64_t c = left % kGraphChunk ? left % kGraphChunk : kGraphChunk;
+      if ((rc = h->hip(hipGraphLaunch(h->g_steps[c], h->stream), "hipGraphLaunch"))) return rc;
+      h->host_step += c;
+      left -= c;
+    }
     return LBM_OK;
   }
   // On one stream a replayed graph saves host time only (128^3: 1.1 us of host
@@ -1420,19 +1420,20 @@ int lbm_step(lbm_handle* h, int64_t n) {
   // call 34 us of host time replayed, 8 launched), and a captured one costs
   // about 15 us per step once.  So the first steps after a change of the launches
   // are launched directly, and later full chunks are replayed.
+  // A call that fails half way has counted the steps it enqueued.
   for (int64_t left = n; left > 0;) {
+    int64_t c = left % kGraphChunk ? left % kGraphChunk : kGraphChunk;
     if (left >= kGraphChunk && h->direct_steps >= kDirectSteps) {
-      if (!h->g_steps[kGraphChunk] && (rc = capture(h, kGraphChunk, &h->g_steps[kGraphChunk]))) return rc;
-      if ((rc = h->hip(hipGraphLaunch(h->g_steps[kGraphChunk], h->stream), "hipGraphLaunch"))) return rc;
-      left -= kGraphChunk;
-      continue;
+      c = kGraphChunk;
+      if (!h->g_steps[c] && (rc = capture(h, (int)c, &h->g_steps[c]))) return rc;
+      if ((rc = h->hip(hipGraphLaunch(h->g_steps[c], h->stream), "hipGraphLaunch"))) return rc;
+    } else {
+      enqueue_steps(h, c);
+      h->direct_steps += c;
     }
-    const int64_t c = left % kGraphChunk ? left % kGraphChunk : kGraphChunk;
-    enqueue_steps(h, c);
-    h->direct_steps += c;
+    h->host_step += c;
     left -= c;
   }
-  h->host_step += n;
   return h->hip(hipGetLastError(), "kernel launch");
 }
 

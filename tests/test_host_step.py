@@ -1,6 +1,7 @@
 """lbm_step's bookkeeping on the host, against the HIP stand-in of
 tests/hoststub (no GPU, no kernel runs): a call that is refused because the
-caller captures the stream leaves nothing marked as done."""
+caller captures the stream leaves nothing marked as done, and a call that fails
+half way counts exactly the steps that were enqueued."""
 import ctypes as C
 import os
 import subprocess
@@ -90,4 +91,29 @@ lat.step(2)
 assert records()[0] == 3
 lat.step(2)
 assert records()[0] == 3
+""")
+
+
+def test_failed_capture_counts_the_steps_enqueued(stub):
+    _run(stub, """
+lat = handle()
+control(fail_instantiate=1)
+refused(lat.step, 700)
+done = records()[1]
+assert 0 < done < 700 and lat.time == done
+control()
+lat.step(700)
+r = records()
+assert lat.time == done + 700 == r[1] + r[2] and r[3] > 0
+""")
+
+
+def test_failed_replay_counts_the_steps_enqueued(stub):
+    _run(stub, """
+lat = handle()
+lat.step(640)
+control(fail_launch=2)
+refused(lat.step, 320)
+r = records()
+assert lat.time == r[1] + r[2] < 960
 """)
