@@ -814,8 +814,12 @@ __device__ inline void bead_block(const Dev& d, int b, int64_t n) {
   }
   __syncthreads();
   if (tid == 0) {
-    sterm = step_terms(in, cen);
-    d.bterms[b] = sterm;
+    // folded terms are read by the spreading workgroups of this launch, and the
+    // force recorded here is to be the one they spread
+    if (d.folded)
+      sterm = d.bterms[b];
+    else
+      d.bterms[b] = sterm = step_terms(in, cen);
     d.bstate[b].V = cen[4 * in.slot + 3] / 6.0;
   } else if (tid >= 64 && tid < 67) {
     const int a = tid - 64;
@@ -861,7 +865,8 @@ __global__ __launch_bounds__(kStepBlock, 4) void k_step_b(Dev d, int collide, in
 }
 
 // The terms of every bead (one workgroup per bead), for boxes with more beads
-// or patches than a spreading workgroup folds.
+// or patches than a spreading workgroup folds.  The only writer of d.bterms in
+// such a handle: k_step_b's workgroups all read them.
 __global__ __launch_bounds__(64) void k_step_fold(Dev d) {
   __shared__ double cen[12];
   const int b = blockIdx.x;
