@@ -58,7 +58,7 @@ struct AdjWork {
   float* L = nullptr;           // [2][19][pstride] adjoint populations
   float *lu = nullptr, *lF = nullptr;  // [3][pstride]
   int* lstamp = nullptr;        // [ntiles] step whose lambda_u a tile holds
-  double* pos0 = nullptr;       // [3][nm] markers of a segment's first step
+  double* pos0 = nullptr;       // [3][nm] markers of the recomputed step
   int* overflow = nullptr;
   int nsc = 0, max_near = 0;
   hipStream_t side = nullptr;            // reverse sweep: side stream (main: the handle's)
@@ -199,10 +199,11 @@ Dev set_view(const Dev& dS, const AdjSet& S, size_t popn) {
 
 // Recompute of one segment from its checkpoint (already in the set) on stream
 // s: near marks of its first step, then the steps as lbm_step's fused launches.
-// Step i's markers go to pslab[i] (the checkpoint's, or advanced from
-// pslab[i-1]), its bead statistics to bslab[i+1], taking the previous centres
-// (the volume's reference point) from bslab[i]; it marks the near blocks of
-// step i+1 into entry i+1.
+// Step i's markers are advanced from pslab[i-1] into w.pos0 (the first step's are
+// the checkpoint's), which its second launch reads while copying them to pslab[i];
+// its bead statistics go to bslab[i+1], taking the previous centres (the volume's
+// reference point) from bslab[i]; it marks the near blocks of step i+1 into entry
+// i+1.
 void enqueue_recompute(lbm_handle* h, AdjWork& w, const AdjSet& St, const Dev& dS, int m, hipStream_t s) {
   const size_t ps = (size_t)h->pstride, nm = (size_t)h->nm, nb = h->beads.size();
   {
@@ -225,7 +226,7 @@ void enqueue_recompute(lbm_handle* h, AdjWork& w, const AdjSet& St, const Dev& d
     d.mom = St.mom + (size_t)i * h->nodes;
     d.bstate = St.bslab + i * nb;
     d.pos = St.pslab + (i > 0 ? i - 1 : 0) * 3 * nm;
-    d.pos_new = i > 0 ? St.pslab + i * 3 * nm : w.pos0;
+    d.pos_new = w.pos0;
     launch_stream_collide_mom(d, i > 0 ? kLaunchStepA : kLaunchStepFirst, share, s);
     d.bstate = St.bslab + (i + 1) * nb;
     d.pos = St.pslab + i * 3 * nm;
