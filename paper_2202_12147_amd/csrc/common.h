@@ -79,6 +79,12 @@ constexpr int kFoldBeads = 64;
 // limited to kSlabGrid (two per compute unit) over all beads.
 constexpr int kSlabWorkers = 64, kSlabWorkersMin = 8, kSlabGrid = 512;
 constexpr int kFoldPatches = 256;
+// Block counters of the persistent bulk launch: one per XCD (workgroups are
+// dealt to the 8 XCDs round robin) and step parity, each on its own 128-byte
+// line; Dev::work holds kWorkCounters ints.
+constexpr int kXcds = 8;
+constexpr int kWorkStride = 32;
+constexpr int kWorkCounters = 2 * kXcds * kWorkStride;
 constexpr int kPopBlock = 256; // nodes per population block (a power of two: shifts and masks)
 // mark_offset of launch_bead_stats / launch_stats_forces that leaves the near
 // blocks unmarked (the near-block launch marks them)
@@ -253,6 +259,9 @@ struct Dev {
   // lists (near_list[parity][i], near_count[parity]); a block is near when it
   // holds a node within two nodes of a bead's stencil region.  Null elsewhere.
   int* near;
+  // persistent bulk launch: block counters work[parity][group * kWorkStride]
+  // (zero before a step's launch; each launch zeroes the next step's)
+  int* work;
   int* near_list;
   int* near_count;
   int max_near, nsc, sc_bs;

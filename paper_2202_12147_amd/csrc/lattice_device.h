@@ -371,9 +371,11 @@ __device__ inline void sc_load(const Dev& d, const Nbr& o, int64_t base, int64_t
 // scattered runs: 128^3 FP32 launch 48.1 against 50.2 us written through);
 // beside the immersed-boundary kernels they stay written through (plain:
 // step 58.9 against 56.8 us, the L2 taken from the concurrent kernels).
+// `set`: the population set to write (a caller that reads its address before the
+// populations saves a trip to the arguments before the stores).
 // WT: whether the stores are written through, 0 / 1, or 2: as d.small_pops says.
 template <int ST, bool OFF32, bool SERIAL, int WT = 2>
-__device__ inline void sc_store(const Dev& d, const Nbr& o, int64_t base, int64_t n, const float* g) {
+__device__ inline void sc_store(const Dev& d, const Nbr& o, int64_t base, int64_t n, void* set, const float* g) {
   if constexpr (ST == kFp32InPlace) {
     const __amdgpu_buffer_rsrc_t rs = inplace_rsrc(d);
     const uint32_t M = (uint32_t)base * 4u;
@@ -390,7 +392,7 @@ __device__ inline void sc_store(const Dev& d, const Nbr& o, int64_t base, int64_
   } else {
     using IO = PopIO<ST>;
     using T = typename IO::T;
-    T* __restrict__ dst = static_cast<T*>(d.pop[(n + 1) & 1]);
+    T* __restrict__ dst = static_cast<T*>(set);
     T* bq;
     if constexpr (OFF32) {
       // 32-bit byte offsets from the set's start (see pull): one offset
@@ -419,8 +421,8 @@ __device__ inline void sc_store(const Dev& d, const Nbr& o, int64_t base, int64_
 // `avg`: add u to the node's time-average sums (a sampled step).
 // MOM: also record (rho, u) of the node in d.mom.
 template <int ST, bool MOM, bool OFF32, bool SERIAL, int WT = 2>
-__device__ inline void sc_finish(const Dev& d, const Box& B, const Nbr& o, int64_t base, int64_t n, float* g, float Fx,
-                                 float Fy, float Fz, bool forced, bool avg, const AvgSums& a) {
+__device__ inline void sc_finish(const Dev& d, const Box& B, const Nbr& o, int64_t base, int64_t n, void* set, float* g,
+                                 float Fx, float Fy, float Fz, bool forced, bool avg, const AvgSums& a) {
   const int64_t ps = d.pstride;
   const Moments m = moments(g);
   const float ir = inv_density(m.rho);
@@ -448,7 +450,7 @@ __device__ inline void sc_finish(const Dev& d, const Box& B, const Nbr& o, int64
     collide_all<true>(g, m, B.omega, ex, ey, ez, src_a, ux, uy, uz, Fx, Fy, Fz);
   else
     collide_all<false>(g, m, B.omega, ex, ey, ez, src_a, ux, uy, uz, Fx, Fy, Fz);
-  sc_store<ST, OFF32, SERIAL, WT>(d, o, base, n, g);
+  sc_store<ST, OFF32, SERIAL, WT>(d, o, base, n, set, g);
   if (avg) {
     double* __restrict__ acc = d.uavg;
     acc[base] = a.x + (double)ux;
@@ -464,6 +466,7 @@ __device__ inline void sc_node(const Dev& d, const Box& B, int x, int y, int z, 
   static_assert(!MOM || ST != kFp32InPlace, "the in-place storage does not record moments");
   const Nbr o = neighbours(x, y, z, B.nx, B.ny, B.nz);
   const AvgSums a = avg_load(d, base, avg);
+  void* const set = d.pop[(n + 1) & 1];
   float g[kQ];
   sc_load<ST, NTLD, OFF32>(d, o, base, n, g);
   float Fx = B.gx, Fy = B.gy, Fz = B.gz;
@@ -472,7 +475,7 @@ __device__ inline void sc_node(const Dev& d, const Box& B, int x, int y, int z, 
     Fy += d.F[d.pstride + base];
     Fz += d.F[2 * d.pstride + base];
   }
-  sc_finish<ST, MOM, OFF32, SERIAL, WT>(d, B, o, base, n, g, Fx, Fy, Fz, forced, avg, a);
+  sc_finish<ST, MOM, OFF32, SERIAL, WT>(d, B, o, base, n, set, g, Fx, Fy, Fz, forced, avg, a);
 }
 
 // Whether step n adds to the time-average sums (uniform over a launch).

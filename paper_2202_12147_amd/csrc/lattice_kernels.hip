@@ -78,9 +78,13 @@ __global__ __launch_bounds__(BS) void k_stream_collide(Dev d, int remap, int nbl
     if ((int)blockIdx.x < cnt)
       sc_block<ST, BS, NTLD, false>(d, d.near_list[pp * d.max_near + blockIdx.x], n, false, avg);
   } else if constexpr (MODE == kLaunchBulk) {
-    // Persistent launches (resident > 0) walk the blocks statically.  With
-    // `remap` each XCD walks one contiguous range of blocks, else the blocks go
-    // grid-stride (round robin over the XCDs).
+    // Persistent launches (resident > 0) walk the blocks statically here
+    // (FP16 storage; FP32 launches k_stream_collide_claimed instead): FP16
+    // blocks take half the time of FP32 ones and the FP16 step is bound by
+    // the immersed-boundary chain, so claiming blocks costs more than it
+    // balances (58.8 against 57.7 us per 128^3 step).  With `remap` each XCD
+    // walks one contiguous range of blocks, else the blocks go grid-stride
+    // (round robin over the XCDs).
     if (resident && remap) {
       const int per = (nblocks + 7) / 8;  // logical blocks per XCD
       const int xcd = blockIdx.x % 8, g8 = (int)gridDim.x / 8;
@@ -98,6 +102,51 @@ __global__ __launch_bounds__(BS) void k_stream_collide(Dev d, int remap, int nbl
   } else {
     const int blk = logical_block(remap, nblocks);
     if (blk < nblocks) sc_block<ST, BS, NTLD, true>(d, blk, n, false, avg);
+  }
+}
+
+// Persistent bulk launch with claimed blocks (FP32 storage; the same launch
+// mode and arguments as k_stream_collide<..., kLaunchBulk, ...> with resident > 0;
+// a kernel of its own so that the claim slots in LDS are not allocated by the
+// other launches).
+//
+// The workgroups of group g = blockIdx.x mod G (G = 8 when the grid allows:
+// the workgroups of one XCD) claim the group's blocks one at a time from
+// the group's counter, so workgroups slowed by the concurrent
+// immersed-boundary kernels take fewer blocks.  64 boxes of 32 to 96 nodes an
+// edge, 17.6 M nodes, us per step claimed and with a static split: 512/1 706 and
+// 1080, 512/2 872 and 1021, 256/2 700 and 1100, 256/4 884 and 1005 (block /
+// resident; one workgroup per block 685).  The group's blocks are g, g + G,
+// g + 2G, ... (round robin), or, with `remap`, one contiguous range per
+// group.  The claim of the next block is issued before the current block's
+// work, which hides its latency; two claim slots need one barrier per block.
+// Odd steps walk each group's blocks in reverse, so a step starts on the
+// blocks the previous one wrote last, the likeliest to be still in the
+// last-level cache.
+template <int ST, int BS, bool AVG, bool NTLD>
+__global__ __launch_bounds__(BS) void k_stream_collide_claimed(Dev d, int remap, int nblocks, int resident) {
+  (void)resident;
+  const int64_t n = *d.step + d.sub;
+  const int64_t pn = n - 1;  // the step whose bead statistics marked the near blocks
+  const int pf = near_slot(pn);
+  const bool avg = AVG && avg_sampled(d, n);
+  __shared__ int next[2];
+  const int G = min(kXcds, (int)gridDim.x), g = (int)blockIdx.x % G;
+  const int per = (nblocks + G - 1) / G;
+  int* const ctr = d.work + ((int)(n & 1) * kXcds + g) * kWorkStride;
+  if ((int)blockIdx.x < G && threadIdx.x == 0)
+    d.work[((int)((n + 1) & 1) * kXcds + (int)blockIdx.x) * kWorkStride] = 0;
+  if (threadIdx.x == 0) next[0] = atomicAdd(ctr, 1);
+  __syncthreads();
+  for (int i = 0;; ++i) {
+    const int j = next[i & 1];  // uniform over the workgroup
+    if (j >= per) break;
+    // slot (i + 1) & 1 was last read in iteration i - 1, before its barrier
+    if (threadIdx.x == 0) next[(i + 1) & 1] = atomicAdd(ctr, 1);
+    const int jj = (n & 1) ? per - 1 - j : j;
+    const int blk = remap ? g * per + jj : g + G * jj;
+    if (blk < nblocks && d.near[pf * d.nsc + blk] != (int)pn) sc_block<ST, BS, NTLD, false>(d, blk, n, true, avg);
+    __syncthreads();
   }
 }
 
@@ -351,6 +400,15 @@ static void launch_sc_mode(const Dev& d, const ScArgs& p) {
   if (MODE == kLaunchBulk && p.resident > 0) {
     resident = p.resident;
     grid = p.remap ? std::min(grid, p.ncu * resident) / 8 * 8 : std::min(grid, p.ncu * resident);
+  }
+  if (MODE == kLaunchBulk && resident > 0 && ST != kFp16) {
+    if (p.block == 128)
+      launch_k(k_stream_collide_claimed<ST, 128, AVG, NTLD>, grid, 128, p.s, p.ev0, p.ev1, d, p.remap, p.nblocks, resident);
+    else if (p.block == 512)
+      launch_k(k_stream_collide_claimed<ST, 512, AVG, NTLD>, grid, 512, p.s, p.ev0, p.ev1, d, p.remap, p.nblocks, resident);
+    else
+      launch_k(k_stream_collide_claimed<ST, 256, AVG, NTLD>, grid, 256, p.s, p.ev0, p.ev1, d, p.remap, p.nblocks, resident);
+    return;
   }
   if (p.block == 128)
     launch_k(k_stream_collide<ST, 128, MODE, AVG, NTLD>, grid, 128, p.s, p.ev0, p.ev1, d, p.remap, p.nblocks, resident);

@@ -599,6 +599,7 @@ int upload(lbm_handle* h) {
     h->dev.near = h->alloc<int>(kNearSlots * (size_t)nsc_max, rc);
     h->dev.near_list = h->alloc<int>(2 * (size_t)nsc_max, rc);
     h->dev.near_count = h->alloc<int>(2, rc);
+    h->dev.work = h->alloc<int>(kWorkCounters, rc);
   }
   int* const d_patch = h->alloc<int>(P.head.size(), rc);
   int* const d_patch_marker = h->alloc<int>(P.marker.size(), rc);
@@ -879,7 +880,7 @@ int capturing(lbm_handle* h, bool* out) {
 
 // Before stepping resumes: the near tiles of the next step from the current
 // markers (two-stream schedule: bead regions and near blocks under the previous
-// step's parity).  In no graph of the library's own; recorded into a caller's
+// step's parity, and zeroed block counters for the persistent bulk launch).  In no graph of the library's own; recorded into a caller's
 // graph (a handle without graphs), the marks are still to be made.
 int prologue(lbm_handle* h) {
   if (!h->need_prologue || h->swimmers.empty()) return LBM_OK;
@@ -890,6 +891,7 @@ int prologue(lbm_handle* h) {
   if (two_stream(h)) {
     rc = h->hip(hipMemsetAsync(d.near, 0x80, sizeof(int) * kNearSlots * d.nsc, h->stream), "hipMemsetAsync");
     if (!rc) rc = h->hip(hipMemsetAsync(d.near_count, 0, sizeof(int) * 2, h->stream), "hipMemsetAsync");
+    if (!rc) rc = h->hip(hipMemsetAsync(d.work, 0, sizeof(int) * kWorkCounters, h->stream), "hipMemsetAsync");
     if (rc) return rc;
     launch_bead_stats(d, -1, h->stream);
     rc = h->hip(hipGetLastError(), "prologue launch");

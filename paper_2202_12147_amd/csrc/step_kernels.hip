@@ -137,7 +137,7 @@ __device__ inline void step_bulk(const Dev& d, int j, int64_t n) {
     const int tile = B.tile0 + (x / kTile) + B.tx * ((y / kTile) + B.ty * (z / kTile));
     if (d.near_tile[slot * d.ntiles + tile] == (int)n) return;
   }
-  sc_finish<ST, EX == kMoments, kOff32<SZ>, false, kThrough<SZ>>(d, B, o, base, n, g, B.gx, B.gy, B.gz, false, avg,
+  sc_finish<ST, EX == kMoments, kOff32<SZ>, false, kThrough<SZ>>(d, B, o, base, n, d.pop[(n + 1) & 1], g, B.gx, B.gy, B.gz, false, avg,
                                                                  sums);
 }
 
@@ -736,7 +736,7 @@ __device__ inline void spread_block(const Dev& d, int sblk, int collide, int64_t
       d.F[2 * d.pstride + base] = az;
       if (collide) {
         const Nbr o = neighbours(x, y, z, B.nx, B.ny, B.nz);
-        sc_finish<ST, EX == kMoments, kOff32<SZ>, false, kThrough<SZ>>(d, B, o, base, n, g, B.gx + ax, B.gy + ay, B.gz + az, true,
+        sc_finish<ST, EX == kMoments, kOff32<SZ>, false, kThrough<SZ>>(d, B, o, base, n, d.pop[(n + 1) & 1], g, B.gx + ax, B.gy + ay, B.gz + az, true,
                                                              avg, sums);
       }
     }
