@@ -347,11 +347,13 @@ int lbm_kernel_time(lbm_handle* h, double* ms, int64_t* launches);
  * swimmers `resident` >= 0 (any value) runs the fused step, two launches of
  * 512-thread workgroups that hold the immersed-boundary work and the
  * stream-collide of all blocks side by side; -1 runs the immersed-boundary
- * work by itself and then one full-grid launch of the given shape.  FP16
- * storage and batches of more than 64 beads (128 where the population sets take
- * at most 1 GiB) run the immersed-boundary work on a
- * second stream beside a launch of the given shape: one workgroup per block
- * (`resident` 0) or `resident` workgroups per compute unit that walk the blocks.
+ * work by itself and then one full-grid launch of the given shape.  Handles that
+ * do not run the fused step run the immersed-boundary work on a second stream
+ * beside a launch of the given shape: one workgroup per block (`resident` 0) or
+ * `resident` workgroups per compute unit that walk the blocks (FP16) or claim
+ * them one by one (FP32).  These are FP16 storage, boxes of more than 36 beads or
+ * 256 surface patches (a bead of v mesh nodes has v / 32, rounded up), and batches
+ * of more than 64 beads (128 where the population sets take at most 1 GiB).
  * Results are bitwise identical for every choice.  Errors: LBM_EINVAL. */
 int lbm_set_stream_collide_launch(lbm_handle* h, int block, int xcd_remap, int resident);
 /* Algorithmic bytes one stream-collide launch moves (19 populations read and

@@ -4,12 +4,12 @@
 // The forward run is plain stepping (lbm_step) with the populations, markers
 // and bead statistics copied aside every K steps.  Segments are then taken in
 // reverse order: the segment's forward steps are recomputed from its
-// checkpoint on scratch buffers (lbm_step's fused launches, so the trajectory
+// checkpoint on scratch buffers (on lbm_step's schedule, so the trajectory
 // is bitwise the forward one), keeping per step the markers, the
 // bead statistics, the marker forces, the force density with its tile stamps
 // and (rho, u) of every node; then its reverse steps run from last to first.
 // Segment storage is double-buffered: the recompute of segment c - 1 runs on
-// its own stream while the reverse sweep of segment c runs on the
+// its own streams while the reverse sweep of segment c runs on the
 // handle's stream and the adjoint side stream.
 // The handle's own state is only touched by the forward run.
 #include <hip/hip_runtime.h>
@@ -62,8 +62,8 @@ struct AdjWork {
   int* overflow = nullptr;
   int nsc = 0, max_near = 0;
   hipStream_t side = nullptr;            // reverse sweep: side stream (main: the handle's)
-  hipStream_t rmain = nullptr;           // recompute
-  hipEvent_t ev[12] = {};  // 4-7, 10, 11: reverse
+  hipStream_t rmain = nullptr, rside = nullptr;  // recompute (rside: two-stream schedule)
+  hipEvent_t ev[12] = {};  // 0-3, 8, 9: recompute on two streams; 4-7, 10, 11: reverse
   hipEvent_t rec_done[2] = {}, rev_done[2] = {}, start = nullptr;
   // recompute graphs by (length, set); reverse-sweep graphs by (objective
   // swimmer, length, parity, set): the swimmer is a kernel argument of the
@@ -73,7 +73,7 @@ struct AdjWork {
   float* lr32 = nullptr;
 
   ~AdjWork() {
-    for (hipStream_t q : {side, rmain})
+    for (hipStream_t q : {side, rmain, rside})
       if (q) (void)hipStreamSynchronize(q);
     for (auto* g : {&rgraphs, &vgraphs})
       for (auto& kv : *g)
@@ -82,7 +82,7 @@ struct AdjWork {
       if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : {rec_done[0], rec_done[1], rev_done[0], rev_done[1], start})
       if (e) (void)hipEventDestroy(e);
-    for (hipStream_t q : {side, rmain})
+    for (hipStream_t q : {side, rmain, rside})
       if (q) (void)hipStreamDestroy(q);
     for (void* p : allocs) (void)hipFree(p);
   }
@@ -156,6 +156,9 @@ int ensure_work(lbm_handle* h, int64_t nck, int K) {
   w->lr32 = w->alloc<float>(3 * nm, rc);
   for (hipStream_t* q : {&w->side, &w->rmain})
     if (!rc) rc = h->hip(hipStreamCreate(q), "hipStreamCreate");
+  // one stream more takes a hardware queue from the others (96^3: 13.5 ms per 100
+  // steps with it idle, 12.7 without), so only where it is used
+  if (!rc && two_stream(h)) rc = h->hip(hipStreamCreate(&w->rside), "hipStreamCreate");
   for (hipEvent_t& e : w->ev)
     if (!rc) rc = h->hip(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreateWithFlags");
   for (hipEvent_t* e : {&w->rec_done[0], &w->rec_done[1], &w->rev_done[0], &w->rev_done[1], &w->start})
@@ -182,6 +185,18 @@ Dev with_near(Dev d, const Dev& n) {
   d.near = n.near;
   d.near_list = n.near_list;
   d.near_count = n.near_count;
+  return d;
+}
+
+// Advection of segment step i on the two-stream schedule: markers of pslab[i]
+// into pslab[i+1]; the near-count reset of the advection kernel goes to a sink
+// (every entry's counts are cleared at segment start).
+Dev advect_view(const Dev& base, const AdjSet& S, int i, size_t nm) {
+  Dev d = base;
+  d.sub = i + 1;
+  d.pos = S.pslab + i * 3 * nm;
+  d.pos_next = S.pslab + (i + 1) * 3 * nm;
+  d.near_count = S.count_sink;
   return d;
 }
 
@@ -232,6 +247,54 @@ void enqueue_recompute(lbm_handle* h, AdjWork& w, const AdjSet& St, const Dev& d
     d.pos = St.pslab + i * 3 * nm;
     launch_stream_collide_mom(d, kLaunchStepB, share, s);
   }
+}
+
+// The same on the two-stream schedule, on the streams s (main) and S2 (side): the
+// side stream advects step i-1 and runs step i's bead statistics, forces,
+// spreading and near-block launch (after the bulk launch of step i-1), the main
+// stream the bulk launch of step i (after the near-block launch of step i-1).
+// Step i reads the markers of pslab[i] and advects them into pslab[i+1].
+void enqueue_recompute_two(lbm_handle* h, AdjWork& w, const AdjSet& St, const Dev& dS, int m, int nblocks,
+                           hipStream_t s, hipStream_t S2) {
+  const size_t ps = (size_t)h->pstride, nm = (size_t)h->nm, nb = h->beads.size();
+  hipEvent_t* ev = w.ev;
+  {
+    Dev d = near_view(dS, w, St, 0);
+    d.pos = St.pslab;
+    d.bstate_prev = St.bslab;
+    d.bstate = St.bsink;
+    launch_bead_stats(d, -1, s);
+  }
+  (void)hipEventRecord(ev[8], s);
+  (void)hipStreamWaitEvent(S2, ev[8], 0);
+  for (int i = 0; i < m; ++i) {
+    Dev d = dS;
+    d.sub = i;
+    d.pos = St.pslab + i * 3 * nm;
+    d.bstate_prev = St.bslab + i * nb;
+    d.bstate = St.bslab + (i + 1) * nb;
+    d.fm = St.fslab + i * 3 * nm;
+    d.F = St.Fslab + (size_t)i * 3 * ps;
+    d.stamp = St.stslab + (size_t)i * h->ntiles;
+    d.mom = St.mom + (size_t)i * h->nodes;
+    hipEvent_t bulk_now = ev[i & 1], bulk_prev = ev[(i + 1) & 1];
+    hipEvent_t near_now = ev[2 + (i & 1)], near_prev = ev[2 + ((i + 1) & 1)];
+    if (i > 0) launch_interp_advance(advect_view(dS, St, i - 1, nm), S2);
+    const Dev dm = with_near(d, near_view(dS, w, St, i + 1));
+    launch_stats_forces(dm, 0, S2);
+    launch_spread(dm, S2);
+    launch_marker_force_total(dm, dm.fm, S2);  // the step's total forces, read by the reverse sweep
+    const Dev dr = with_near(d, near_view(dS, w, St, i));
+    if (i > 0) (void)hipStreamWaitEvent(s, near_prev, 0);
+    launch_stream_collide_mom(dr, kLaunchBulk, nblocks, s);
+    (void)hipEventRecord(bulk_now, s);
+    if (i > 0) (void)hipStreamWaitEvent(S2, bulk_prev, 0);
+    launch_stream_collide_mom(dr, kLaunchActive, nblocks, S2);
+    (void)hipEventRecord(near_now, S2);
+  }
+  launch_interp_advance(advect_view(dS, St, m - 1, nm), S2);
+  (void)hipEventRecord(ev[9], S2);
+  (void)hipStreamWaitEvent(s, ev[9], 0);
 }
 
 // Reverse steps of a segment, last to first, on the streams s (main) and S2
@@ -365,10 +428,13 @@ int run(lbm_handle* h, const lbm_adjoint_desc* ad, double* J, double* grad) {
                   "hipMemsetAsync");
   }
   if (!rc) rc = h->hip(hipMemsetAsync(w.lstamp, 0x80, sizeof(int) * (size_t)h->ntiles, s), "hipMemsetAsync");
-  // the recompute marks near tiles in the handle's arrays: the forward run's
+  // the fused recompute marks near tiles in the handle's arrays: the forward run's
   // marks of the same steps go first, and stepping marks its own anew afterwards
-  if (!rc) rc = clear_near(h, s);
-  h->need_prologue = true;
+  const bool two = two_stream(h);
+  if (!rc && !two) {
+    rc = clear_near(h, s);
+    h->need_prologue = true;
+  }
   if (!rc) rc = h->hip(hipMemsetAsync(w.overflow, 0, sizeof(int), s), "hipMemsetAsync");
   if (rc) return rc;
   launch_adj_init(set_view(dS, w.set[0], popn), a, s);
@@ -396,7 +462,12 @@ int run(lbm_handle* h, const lbm_adjoint_desc* ad, double* J, double* grad) {
     launch_set_step(St.step, n0, r);
     const Dev dv = set_view(dS, St, popn);
     e = enqueue_or_replay(h, w.rgraphs, 4 * (int64_t)m + k, r,
-                          [&] { enqueue_recompute(h, w, St, dv, m, r); });
+                          [&] {
+                            if (two)
+                              enqueue_recompute_two(h, w, St, dv, m, nblocks, r, w.rside);
+                            else
+                              enqueue_recompute(h, w, St, dv, m, r);
+                          });
     if (!e) e = h->hip(hipEventRecord(w.rec_done[k], r), "hipEventRecord");
     return e;
   };

@@ -314,7 +314,6 @@ struct Dev {
   int4* slab_list;             // slabs of the step, box after box (k_step_a's list workgroups)
   int* slab_count;             // [nboxes]
   int step_spread_blocks;
-  int folded;               // 1: the bead terms come from k_step_fold
   int tick;                 // steps the closing advection adds to the step counter
   // (rho, u) of every node, written by the moment-recording stream-collide
   // variant only (segment recompute of the adjoint)
@@ -348,7 +347,9 @@ void launch_stream_collide(const Dev& d, int storage, int mode, int block, int n
                            int resident, int ncu, hipStream_t s, hipEvent_t ev0 = nullptr,
                            hipEvent_t ev1 = nullptr);
 // Stream-collide (FP32 storage, single box) that also writes each
-// node's (rho, u_x, u_y, u_z) to d.mom, in the step modes above.
+// node's (rho, u_x, u_y, u_z) to d.mom, in the step modes above, or with
+// workgroups of kScBlock nodes in the modes kLaunchBulk and kLaunchActive
+// (nblocks: node blocks of the box).
 void launch_stream_collide_mom(const Dev& d, int mode, int nblocks, hipStream_t s);
 void launch_tick(const Dev& d, int count, hipStream_t s);
 // Node fields of the current state: velocity and density, or, with d.px_buf, the

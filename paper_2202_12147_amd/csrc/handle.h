@@ -67,6 +67,7 @@ struct lbm_handle {
   int64_t nodes = 0, pstride = 0;
   int ntiles = 0, sc_blocks = 0, spread_blocks = 0, out_blocks = 0;
   int sc_block = 512, sc_remap = 0, sc_resident = 1;  // stream-collide launch shape (set per handle at creation)
+  bool sc_chosen = false;           // the caller set the launch shape
   int ncu = 256;                                        // compute units of the device
   bool uploaded = false, stepped = false;
   int64_t host_step = 0;  // steps enqueued
@@ -96,6 +97,7 @@ struct lbm_handle {
   int *d_lane_elem = nullptr, *d_lane_v = nullptr;
   int* d_overflow = nullptr;
   int* d_spread_info = nullptr;  // [spread block][8], see Dev::spread_info
+  bool two = false;                // steps on the two-stream schedule (upload)
   bool need_prologue = true;
   hipStream_t side = nullptr;      // two-stream schedule: the markers' chain, forked from `stream` every step
   std::vector<hipEvent_t> step_events;  // per chunk step: bulk done, near blocks done; + one fork
@@ -138,6 +140,8 @@ namespace lbmib {
 namespace rt {
 
 int element_bytes(const lbm_handle* h);
+// Whether the handle steps on the two-stream schedule.
+bool two_stream(const lbm_handle* h);
 // Blocks of a fused step's first launch; clearing of the near-tile marks.
 int step_share(const lbm_handle* h);
 int clear_near(lbm_handle* h, hipStream_t s);

@@ -371,11 +371,10 @@ __device__ inline void sc_load(const Dev& d, const Nbr& o, int64_t base, int64_t
 // scattered runs: 128^3 FP32 launch 48.1 against 50.2 us written through);
 // beside the immersed-boundary kernels they stay written through (plain:
 // step 58.9 against 56.8 us, the L2 taken from the concurrent kernels).
-// `set`: the population set to write (a caller that reads its address before the
-// populations saves a trip to the arguments before the stores).
 // WT: whether the stores are written through, 0 / 1, or 2: as d.small_pops says.
-template <int ST, bool OFF32, bool SERIAL, int WT = 2>
-__device__ inline void sc_store(const Dev& d, const Nbr& o, int64_t base, int64_t n, void* set, const float* g) {
+// EARLY: the population set to write is `set`, else it is looked up here.
+template <int ST, bool OFF32, bool SERIAL, int WT = 2, bool EARLY = false>
+__device__ inline void sc_store(const Dev& d, const Nbr& o, int64_t base, int64_t n, const float* g, void* set) {
   if constexpr (ST == kFp32InPlace) {
     const __amdgpu_buffer_rsrc_t rs = inplace_rsrc(d);
     const uint32_t M = (uint32_t)base * 4u;
@@ -392,7 +391,7 @@ __device__ inline void sc_store(const Dev& d, const Nbr& o, int64_t base, int64_
   } else {
     using IO = PopIO<ST>;
     using T = typename IO::T;
-    T* __restrict__ dst = static_cast<T*>(set);
+    T* __restrict__ dst = static_cast<T*>(EARLY ? set : d.pop[(n + 1) & 1]);
     T* bq;
     if constexpr (OFF32) {
       // 32-bit byte offsets from the set's start (see pull): one offset
@@ -420,9 +419,9 @@ __device__ inline void sc_store(const Dev& d, const Nbr& o, int64_t base, int64_
 // `forced`: write u at this node (markers may interpolate there).
 // `avg`: add u to the node's time-average sums (a sampled step).
 // MOM: also record (rho, u) of the node in d.mom.
-template <int ST, bool MOM, bool OFF32, bool SERIAL, int WT = 2>
-__device__ inline void sc_finish(const Dev& d, const Box& B, const Nbr& o, int64_t base, int64_t n, void* set, float* g,
-                                 float Fx, float Fy, float Fz, bool forced, bool avg, const AvgSums& a) {
+template <int ST, bool MOM, bool OFF32, bool SERIAL, int WT = 2, bool EARLY = false>
+__device__ inline void sc_finish(const Dev& d, const Box& B, const Nbr& o, int64_t base, int64_t n, float* g, float Fx,
+                                 float Fy, float Fz, bool forced, bool avg, const AvgSums& a, void* set = nullptr) {
   const int64_t ps = d.pstride;
   const Moments m = moments(g);
   const float ir = inv_density(m.rho);
@@ -450,7 +449,7 @@ __device__ inline void sc_finish(const Dev& d, const Box& B, const Nbr& o, int64
     collide_all<true>(g, m, B.omega, ex, ey, ez, src_a, ux, uy, uz, Fx, Fy, Fz);
   else
     collide_all<false>(g, m, B.omega, ex, ey, ez, src_a, ux, uy, uz, Fx, Fy, Fz);
-  sc_store<ST, OFF32, SERIAL, WT>(d, o, base, n, set, g);
+  sc_store<ST, OFF32, SERIAL, WT, EARLY>(d, o, base, n, g, set);
   if (avg) {
     double* __restrict__ acc = d.uavg;
     acc[base] = a.x + (double)ux;
@@ -460,13 +459,17 @@ __device__ inline void sc_finish(const Dev& d, const Box& B, const Nbr& o, int64
 }
 
 // One node: `forced` nodes read the spread force density F and write u.
-template <int ST, bool MOM = false, bool NTLD = true, bool OFF32 = false, bool SERIAL = false, int WT = 2>
+// EARLY: the address of the set to write is looked up before the populations are
+// loaded, not before the stores, which a persistent workgroup's next block waits for
+// (64 boxes, 17.6 M nodes, one per compute unit: 705 us per step, else 730; one
+// workgroup per block gains nothing).
+template <int ST, bool MOM = false, bool NTLD = true, bool OFF32 = false, bool SERIAL = false, bool EARLY = false>
 __device__ inline void sc_node(const Dev& d, const Box& B, int x, int y, int z, int64_t base, int64_t n, bool forced,
                                bool avg) {
   static_assert(!MOM || ST != kFp32InPlace, "the in-place storage does not record moments");
   const Nbr o = neighbours(x, y, z, B.nx, B.ny, B.nz);
   const AvgSums a = avg_load(d, base, avg);
-  void* const set = d.pop[(n + 1) & 1];
+  void* const set = EARLY ? d.pop[(n + 1) & 1] : nullptr;
   float g[kQ];
   sc_load<ST, NTLD, OFF32>(d, o, base, n, g);
   float Fx = B.gx, Fy = B.gy, Fz = B.gz;
@@ -475,7 +478,7 @@ __device__ inline void sc_node(const Dev& d, const Box& B, int x, int y, int z, 
     Fy += d.F[d.pstride + base];
     Fz += d.F[2 * d.pstride + base];
   }
-  sc_finish<ST, MOM, OFF32, SERIAL, WT>(d, B, o, base, n, set, g, Fx, Fy, Fz, forced, avg, a);
+  sc_finish<ST, MOM, OFF32, SERIAL, 2, EARLY>(d, B, o, base, n, g, Fx, Fy, Fz, forced, avg, a, set);
 }
 
 // Whether step n adds to the time-average sums (uniform over a launch).
@@ -486,7 +489,7 @@ __device__ inline bool avg_sampled(const Dev& d, int64_t n) {
 // One block of BS nodes.  `bulk`: none of its nodes is forced (every node a
 // stencil reaches lies in a near block, and an active tile's other nodes carry
 // F = 0).
-template <int ST, int BS, bool NTLD, bool SERIAL>
+template <int ST, int BS, bool NTLD, bool SERIAL, bool MOM = false, bool EARLY = false>
 __device__ inline void sc_block(const Dev& d, int blk, int64_t n, bool bulk, bool avg) {
   const int b = d.nboxes == 1 ? 0 : d.sc_block_box[blk];
   const Box B = d.boxes[b];
@@ -505,9 +508,9 @@ __device__ inline void sc_block(const Dev& d, int blk, int64_t n, bool bulk, boo
   // the two addressing forms as separate code (a population set below 4 GiB
   // takes 32-bit offsets; the in-place set always does)
   if (ST == kFp32InPlace || d.pops32)
-    sc_node<ST, false, NTLD, true, SERIAL>(d, B, x, y, z, B.node0 + id, n, forced, avg);
+    sc_node<ST, MOM, NTLD, true, SERIAL, EARLY>(d, B, x, y, z, B.node0 + id, n, forced, avg);
   else
-    sc_node<ST, false, NTLD, false, SERIAL>(d, B, x, y, z, B.node0 + id, n, forced, avg);
+    sc_node<ST, MOM, NTLD, false, SERIAL, EARLY>(d, B, x, y, z, B.node0 + id, n, forced, avg);
 }
 
 }  // namespace

@@ -145,8 +145,27 @@ __global__ __launch_bounds__(BS) void k_stream_collide_claimed(Dev d, int remap,
     if (threadIdx.x == 0) next[(i + 1) & 1] = atomicAdd(ctr, 1);
     const int jj = (n & 1) ? per - 1 - j : j;
     const int blk = remap ? g * per + jj : g + G * jj;
-    if (blk < nblocks && d.near[pf * d.nsc + blk] != (int)pn) sc_block<ST, BS, NTLD, false>(d, blk, n, true, avg);
+    if (blk < nblocks && d.near[pf * d.nsc + blk] != (int)pn)
+      sc_block<ST, BS, NTLD, false, false, true>(d, blk, n, true, avg);
     __syncthreads();
+  }
+}
+
+// FP32, recording (rho, u) per node (segment recompute of the adjoint), in the
+// two modes of the two-stream schedule, workgroups of kScBlock nodes.
+template <int MODE>
+__global__ __launch_bounds__(kScBlock) void k_stream_collide_mom(Dev d, int nblocks) {
+  const int64_t n = *d.step + d.sub;
+  const int64_t pn = n - 1;
+  const int pp = (int)(pn & 1), pf = near_slot(pn);
+  if constexpr (MODE == kLaunchActive) {
+    const int cnt = min(d.near_count[pp], d.max_near);
+    if ((int)blockIdx.x < cnt)
+      sc_block<kFp32, kScBlock, true, false, true>(d, d.near_list[pp * d.max_near + blockIdx.x], n, false, false);
+  } else {
+    const int blk = blockIdx.x;
+    if (blk < nblocks && d.near[pf * d.nsc + blk] != (int)pn)
+      sc_block<kFp32, kScBlock, true, false, true>(d, blk, n, true, false);
   }
 }
 
@@ -465,7 +484,12 @@ void launch_stream_collide(const Dev& d, int storage, int mode, int block, int n
 }
 
 void launch_stream_collide_mom(const Dev& d, int mode, int nblocks, hipStream_t s) {
-  launch_step_mom(d, mode, nblocks, s);
+  if (mode == kLaunchActive)
+    hipLaunchKernelGGL(k_stream_collide_mom<kLaunchActive>, dim3(d.max_near), dim3(kScBlock), 0, s, d, nblocks);
+  else if (mode == kLaunchBulk)
+    hipLaunchKernelGGL(k_stream_collide_mom<kLaunchBulk>, dim3(nblocks), dim3(kScBlock), 0, s, d, nblocks);
+  else
+    launch_step_mom(d, mode, nblocks, s);
 }
 
 void launch_tick(const Dev& d, int count, hipStream_t s) {

@@ -258,18 +258,47 @@ void set_near_bounds(lbm_handle* h) {
 //    a force changes which way populations are rounded, so the velocity field
 //    of a run would move by 1e-4 (its own distance from the FP64 result) against
 //    its earlier values.
+//  - boxes of many beads: the spreading workgroups of a box all fold the terms of
+//    its beads.  us per step, two-stream and fused, beads of 12 to 162 nodes: 36
+//    beads in 64^3 55-69 and 27-41, in 96^3 60-73 and 37-58, in 128^3 69-84 and
+//    63-77; 48 in 96^3 61-71 and 65-72; 42 in 256x128x128 116-139 and 112-136; 63
+//    there 125-131 and 134-146.
+//  - boxes of more surface patches than a spreading workgroup folds.  With the
+//    folding in a kernel of its own, a swimmer of level-5 meshes (963 patches) in
+//    96x48x48 215 and 251, in 128^3 220 and 346, in 256x128x128 278 and 383; at the
+//    bound, level 4 (243 patches), 75 and 54, 107 and 107, 152 and 144; four
+//    swimmers of level 3 (252 patches) in 96^3 74 and 57, in 128^3 93 and 82.
 //  - batches of many beads: there the number of the markers' workgroups decides,
 //    not their latency, and the fused step's patches advance their border nodes
 //    twice.  Up to kWriteThroughBytes of populations: 24 boxes, 1.7 M nodes 127 us
 //    per step against 106 fused; 32 boxes, 5.6 M 297 and 271; 40 boxes, 6.7 M 358
 //    and 344; 60 boxes, 6.6 M 259 and 291.  Beyond: 16 boxes 254 and 237; 32 boxes,
 //    11.8 M 441 and 522; 40 boxes, 7.5 M 323 and 361.
-constexpr int kFusedBatchBeads = 64, kFusedBatchBeadsSmall = 128;
-bool two_stream(const lbm_handle* h) {
+constexpr int kFusedBoxBeads = 36, kFusedBatchBeads = 64, kFusedBatchBeadsSmall = 128;
+static_assert(kFusedBoxBeads <= kFoldBeads, "the beads of a box fit its spreading workgroups' tables");
+bool choose_two_stream(const lbm_handle* h) {
   if (h->swimmers.empty()) return false;
   const int most = h->dev.small_pops ? kFusedBatchBeadsSmall : kFusedBatchBeads;
-  return h->storage == LBM_FP16_SHIFTED || (h->boxes.size() > 1 && h->beads.size() > (size_t)most);
+  if (h->storage == LBM_FP16_SHIFTED || (h->boxes.size() > 1 && h->beads.size() > (size_t)most)) return true;
+  std::vector<int> beads(h->boxes.size()), patches(h->boxes.size());
+  for (const Bead& b : h->beads) {
+    beads[b.box] += 1;
+    patches[b.box] += (b.nv + kPatchOwn - 1) / kPatchOwn;
+  }
+  return *std::max_element(beads.begin(), beads.end()) > kFusedBoxBeads ||
+         *std::max_element(patches.begin(), patches.end()) > kFoldPatches;
 }
+
+bool two_stream(const lbm_handle* h) { return h->two; }
+
+// The bulk launch of a single FP32 box on the two-stream schedule, where the caller
+// has chosen none: one persistent workgroup per compute unit, which leaves the
+// others' places to the markers' kernels, or one workgroup per block, which streams
+// faster.  The markers' share of the work decides.  us per step, persistent and
+// per block: 160^3, 9630 markers (425 nodes each) 145 and 164; 512x256x256, 61.6 k
+// (545) 1032 and 1130; 192^3, 11.6 k (612) 231 and 228; 256^3, 23.1 k (726) 547 and
+// 472; 512x256x256, 30.8 k (1089) 1087 and 921.
+constexpr int64_t kPersistentNodesPerMarker = 600;
 
 // ---- surface patches (Dev::patch) ------------------------------------------------
 struct Patches {
@@ -436,6 +465,9 @@ bool build_patches(lbm_handle* h, const std::vector<int>& lane_elem, const std::
 int upload(lbm_handle* h) {
   if (h->uploaded) return LBM_OK;
   int rc = LBM_OK;
+  h->two = choose_two_stream(h);
+  if (h->two && !h->sc_chosen && h->boxes.size() == 1 && h->storage != LBM_FP16_SHIFTED)
+    h->sc_resident = h->nodes < kPersistentNodesPerMarker * h->nm ? 1 : 0;
   const int nm = h->nm;
   const int ntri = (int)h->tri.size() / 3, nh = (int)h->hinge.size() / 4;
   // per-triangle reference geometry and per-vertex incidence lists
@@ -523,7 +555,6 @@ int upload(lbm_handle* h) {
   const int npatch = (int)P.head.size() / 4;
   std::vector<int> step_spread, step_owner, step_first(h->boxes.size());
   std::vector<StepBox> step_box(h->boxes.size());
-  bool folded = false;
   int64_t slabs = 0;
   // Spreading workgroups per bead.  Each first folds its box's bead terms and then
   // walks its share of the slabs.  Few beads leave the chip idle, so a slab or two
@@ -551,7 +582,6 @@ int upload(lbm_handle* h) {
     sx.npatch = last.patch0 + last.npatch - first.patch0;
     sx.m0 = first.first;
     sx.m_end = last.first + last.nv;
-    if (B.nbeads > kFoldBeads || sx.npatch > kFoldPatches) folded = true;
     int64_t mine = 0;
     for (int b = B.bead0; b < B.bead0 + B.nbeads; ++b)
       mine += (int64_t)h->beads[b].tiles_x * h->beads[b].tiles_y * h->beads[b].tiles_z * kSlabParts;
@@ -722,7 +752,6 @@ int upload(lbm_handle* h) {
   d.step_spread = reinterpret_cast<const int2*>(d_step_spread);
   d.step_box = d_step_box;
   d.step_spread_blocks = (int)step_spread.size() / 2;
-  d.folded = folded ? 1 : 0;
   if (two_stream(h)) {
     set_near_bounds(h);
     rc = h->hip(hipStreamCreate(&h->side), "hipStreamCreate");
@@ -753,7 +782,7 @@ void timing_pair(lbm_handle* h, hipEvent_t* e0, hipEvent_t* e1) {
   *e1 = h->ev_pool[h->ev_used++];
 }
 
-// FP16 storage: the side stream runs the immersed-boundary chain of each step --
+// Two-stream schedule: the side stream runs the immersed-boundary chain of each step --
 // advection of the previous step, bead statistics, nodal forces, spreading --
 // and then the near-block launch, while the main stream streams and collides
 // every node away from the swimmers; in serial order (resident < 0) the chain
@@ -1127,8 +1156,9 @@ int create_boxes(const lbm_box_desc* boxes, int nboxes, const lbm_opts* opts, lb
   // storage, one box: two persistent 256-node workgroups per CU while both
   // population sets fit the 256 MB last-level cache (128^3 51.1 us per step,
   // 51.8 non-persistent at 512 nodes), above it one 512-node workgroup per
-  // block (256x128x128 73.5 us, 117.1 persistent).  The other storages use it
-  // for launches without swimmers and the serial order only.
+  // block (256x128x128 73.5 us, 117.1 persistent).  FP32 boxes on the two-stream
+  // schedule: kPersistentNodesPerMarker.  Elsewhere it serves launches without
+  // swimmers and the serial order only.
   h->sc_block = 512;
   h->sc_remap = 0;
   h->sc_resident = 0;
@@ -1817,6 +1847,7 @@ int lbm_set_stream_collide_launch(lbm_handle* h, int block, int xcd_remap, int r
   h->sc_block = block;
   h->sc_remap = xcd_remap ? 1 : 0;
   h->sc_resident = resident;
+  h->sc_chosen = true;
   rc = build_sc_tables(h);
   if (rc) return rc;
   if (h->uploaded && two_stream(h)) set_near_bounds(h);
@@ -1869,6 +1900,7 @@ size_t snapshot_bytes(const Snapshot& S) {
 }
 
 int element_bytes(const lbm_handle* h) { return ::element_bytes(h); }
+bool two_stream(const lbm_handle* h) { return ::two_stream(h); }
 int step_share(const lbm_handle* h) { return ::step_share(h); }
 int clear_near(lbm_handle* h, hipStream_t s) { return ::clear_near(h, s); }
 int upload(lbm_handle* h) { return ::upload(h); }

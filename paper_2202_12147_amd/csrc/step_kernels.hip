@@ -137,7 +137,7 @@ __device__ inline void step_bulk(const Dev& d, int j, int64_t n) {
     const int tile = B.tile0 + (x / kTile) + B.tx * ((y / kTile) + B.ty * (z / kTile));
     if (d.near_tile[slot * d.ntiles + tile] == (int)n) return;
   }
-  sc_finish<ST, EX == kMoments, kOff32<SZ>, false, kThrough<SZ>>(d, B, o, base, n, d.pop[(n + 1) & 1], g, B.gx, B.gy, B.gz, false, avg,
+  sc_finish<ST, EX == kMoments, kOff32<SZ>, false, kThrough<SZ>>(d, B, o, base, n, g, B.gx, B.gy, B.gz, false, avg,
                                                                  sums);
 }
 
@@ -399,42 +399,56 @@ __device__ inline bool near_covers(const NearRange& s, int tx, int ty, int tz, c
 // ---- slab list ------------------------------------------------------------------------
 // The slabs of step n in box `box`, from the near ranges: one entry per z slab
 // of every near tile, {tile of the box * slabs per tile + slab, first marker of the
-// first bead whose range holds the tile, the holding beads among the box's
-// first 64 (two words)}.  One workgroup; the order does not matter, since slabs
-// are independent.
+// first bead whose range holds the tile, the holding beads of the box (two
+// words)}.  One workgroup; the order does not matter, since slabs are independent.
+// k_step_b waits for it, so the tiles of all beads are dealt to the threads at
+// once, and what is left serial is one test per bead.  us per step, bead after
+// bead and at once: 8 swimmers of 162-node beads in 96^3 151.6 and 47.0, in 128^3
+// 168.5 and 71.5; 4 in 64^3 58.0 and 26.7; 2 in 96^3 36.9 and 33.6.
 __device__ inline void list_block(const Dev& d, int box, int64_t n) {
   __shared__ NearRange range[kFoldBeads];
+  __shared__ int end[kFoldBeads];  // tiles of the beads up to this one
   __shared__ int count;
   const int tid = threadIdx.x;
   const StepBox X = d.step_box[box];
   const Box B = d.boxes[box];
-  const NearRange* const ranges = d.near_range + (n & 1) * d.nbeads + X.bead0;
-  if (tid < min(X.nbeads, kFoldBeads)) range[tid] = ranges[tid];
-  if (tid == 0) count = 0;
-  __syncthreads();
-  for (int b = 0; b < X.nbeads; ++b) {
-    const NearRange S = b < kFoldBeads ? range[b] : ranges[b];
-    const int items = S.cnt[0] * S.cnt[1] * S.cnt[2];
-    for (int i = tid; i < items; i += kStepBlock) {
-      int tx = S.t0[0] + i % S.cnt[0], ty = S.t0[1] + (i / S.cnt[0]) % S.cnt[1], tz = S.t0[2] + i / (S.cnt[0] * S.cnt[1]);
-      if (tx >= B.tx) tx -= B.tx;
-      if (ty >= B.ty) ty -= B.ty;
-      if (tz >= B.tz) tz -= B.tz;
-      unsigned long long cover = 0;
-      bool taken = false;  // an earlier bead's range holds the tile
-      for (int j = 0; j < X.nbeads && (j <= b || j < kFoldBeads); ++j) {
-        const bool in = near_covers(j < kFoldBeads ? range[j] : ranges[j], tx, ty, tz, B);
-        if (j < b) taken = taken || in;
-        if (in && j < kFoldBeads) cover |= 1ull << j;
-      }
-      if (taken) continue;
-      const int slabs = (min(kTile, B.nz - tz * kTile) + kSlabLayers - 1) / kSlabLayers;
-      const int at = atomicAdd(&count, slabs);
-      const int first = d.beads[X.bead0 + b].first;
-      for (int p = 0; p < slabs; ++p)
-        d.slab_list[X.list0 + at + p] = make_int4((tx + B.tx * (ty + B.ty * tz)) * kSlabParts + p, first,
-                                                  (int)(uint32_t)cover, (int)(uint32_t)(cover >> 32));
+  static_assert(kFoldBeads == 64, "a bead per lane of the first wavefront, a bit of the cover mask each");
+  if (tid < kFoldBeads) {
+    int tiles = 0;
+    if (tid < X.nbeads) {
+      const NearRange r = d.near_range[(n & 1) * d.nbeads + X.bead0 + tid];
+      range[tid] = r;
+      tiles = r.cnt[0] * r.cnt[1] * r.cnt[2];
     }
+#pragma unroll
+    for (int s = 1; s < 64; s <<= 1) {
+      const int below = __shfl_up(tiles, s, 64);
+      if (tid >= s) tiles += below;
+    }
+    end[tid] = tiles;
+    if (tid == 0) count = 0;
+  }
+  __syncthreads();
+  const int total = end[kFoldBeads - 1];
+  int b = 0;
+  for (int i = tid; i < total; i += kStepBlock) {
+    while (i >= end[b]) ++b;
+    const NearRange S = range[b];
+    const int t = i - (b > 0 ? end[b - 1] : 0);
+    int tx = S.t0[0] + t % S.cnt[0], ty = S.t0[1] + (t / S.cnt[0]) % S.cnt[1], tz = S.t0[2] + t / (S.cnt[0] * S.cnt[1]);
+    if (tx >= B.tx) tx -= B.tx;
+    if (ty >= B.ty) ty -= B.ty;
+    if (tz >= B.tz) tz -= B.tz;
+    unsigned long long cover = 0;
+    for (int j = 0; j < X.nbeads; ++j)
+      if (near_covers(range[j], tx, ty, tz, B)) cover |= 1ull << j;
+    if (cover & ((1ull << b) - 1)) continue;  // an earlier bead's range holds the tile
+    const int slabs = (min(kTile, B.nz - tz * kTile) + kSlabLayers - 1) / kSlabLayers;
+    const int at = atomicAdd(&count, slabs);
+    const int first = d.beads[X.bead0 + b].first;
+    for (int p = 0; p < slabs; ++p)
+      d.slab_list[X.list0 + at + p] = make_int4((tx + B.tx * (ty + B.ty * tz)) * kSlabParts + p, first,
+                                                (int)(uint32_t)cover, (int)(uint32_t)(cover >> 32));
   }
   __syncthreads();
   if (tid == 0) d.slab_count[box] = count;
@@ -560,9 +574,8 @@ __device__ inline void spread_block(const Dev& d, int sblk, int collide, int64_t
   StepMarker q;
   if (one_chunk) q.load(d, X.m0 + tid, m_end);
   int4 entry = uniform(d.slab_list[X.list0 + min(c, max(count - 1, 0))]);
-  const NearRange* const ranges = d.near_range + (n & 1) * d.nbeads + bead0;  // boxes of more than 64 beads
   const bool avg = EX == kAverage && avg_sampled(d, n);
-  // markers of the box's first 64 beads, by lane
+  // markers of the box's beads, by lane
   const int lane_first = lane < nb ? d.beads[bead0 + lane].first : 0x7fffffff;
   const int lane_end = lane < nb ? lane_first + d.beads[bead0 + lane].nv : 0;
   // what the bead terms are made of, loaded with the ranges and the markers
@@ -571,39 +584,35 @@ __device__ inline void spread_block(const Dev& d, int sblk, int collide, int64_t
   double inv_nv = 0.0;
   TermInputs in{};
   static_assert(4 * kFoldPatches <= 2 * kStepBlock && kFoldBeads <= 64, "patch values per thread");
-  if (!d.folded) {
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int t = r * kStepBlock + tid;
-      if (t < 4 * X.npatch) pv[r] = patch_value(d, X.patch0 + (t >> 2), t & 3);
-    }
-    if (tid < 4 * nb) {
-      const Bead& bd = d.beads[bead0 + (tid >> 2)];
-      p0 = bd.patch0 - X.patch0;
-      np = bd.npatch;
-      inv_nv = bd.inv_nv;
-    }
-    if (tid < nb) in = term_inputs(d, bead0 + tid);
+  for (int r = 0; r < 2; ++r) {
+    const int t = r * kStepBlock + tid;
+    if (t < 4 * X.npatch) pv[r] = patch_value(d, X.patch0 + (t >> 2), t & 3);
   }
+  if (tid < 4 * nb) {
+    const Bead& bd = d.beads[bead0 + (tid >> 2)];
+    p0 = bd.patch0 - X.patch0;
+    np = bd.npatch;
+    inv_nv = bd.inv_nv;
+  }
+  if (tid < nb) in = term_inputs(d, bead0 + tid);
   if (c >= count) return;
-  if (!d.folded) {
-    double* const pbuf = reinterpret_cast<double*>(ent);
+  double* const pbuf = reinterpret_cast<double*>(ent);
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const int t = r * kStepBlock + tid;
-      if (t < 4 * X.npatch) pbuf[t] = pv[r];
-    }
-    __syncthreads();
-    if (tid < 4 * nb) {
-      const int k = tid & 3;
-      double v = 0.0;
-#pragma unroll 4
-      for (int j = 0; j < np; ++j) v += pbuf[4 * (p0 + j) + k];
-      fv[tid] = k < 3 ? v * inv_nv : v;
-    }
-    __syncthreads();
-    if (tid < nb) terms[tid] = step_terms(in, fv + 4 * (tid - in.slot));
+  for (int r = 0; r < 2; ++r) {
+    const int t = r * kStepBlock + tid;
+    if (t < 4 * X.npatch) pbuf[t] = pv[r];
   }
+  __syncthreads();
+  if (tid < 4 * nb) {
+    const int k = tid & 3;
+    double v = 0.0;
+#pragma unroll 4
+    for (int j = 0; j < np; ++j) v += pbuf[4 * (p0 + j) + k];
+    fv[tid] = k < 3 ? v * inv_nv : v;
+  }
+  __syncthreads();
+  if (tid < nb) terms[tid] = step_terms(in, fv + 4 * (tid - in.slot));
   for (;;) {
     const int tile = entry.x / kSlabParts, part = entry.x % kSlabParts;
     const int tx = tile % B.tx, ty = (tile / B.tx) % B.ty, tz = tile / (B.tx * B.ty);
@@ -639,12 +648,7 @@ __device__ inline void spread_block(const Dev& d, int sblk, int collide, int64_t
       bool take = q.bead >= 0;
       const int i = q.bead - bead0;
       int off[3], first_node[3];
-      if (take) {
-        if (i < 64)
-          take = (cover >> i) & 1ull;
-        else
-          take = near_covers(ranges[i], tx, ty, tz, B);
-      }
+      take = take && ((cover >> (i & 63)) & 1ull);
       if (take) {
         const int org[3] = {ox, oy, oz}, ext[3] = {ex, ey, ez}, N[3] = {B.nx, B.ny, B.nz};
 #pragma unroll
@@ -667,7 +671,7 @@ __device__ inline void spread_block(const Dev& d, int sblk, int collide, int64_t
       }
       if (take) {
         StepEntry& E = ent[at];
-        const BeadTerms t = d.folded ? d.bterms[q.bead] : terms[i];
+        const BeadTerms t = terms[i];
         float w[3][NW];
 #pragma unroll
         for (int a = 0; a < 3; ++a)
@@ -710,7 +714,7 @@ __device__ inline void spread_block(const Dev& d, int sblk, int collide, int64_t
       int next = at + kStepBlock;
       for (; next < m_end; next += kStepBlock) {
         const bool meets = lane < nb && ((cover >> lane) & 1ull) && lane_first < next + kStepBlock && lane_end > next;
-        if (nb > 64 || __ballot(meets)) break;
+        if (__ballot(meets)) break;
       }
       StepMarker ahead;
       if (next < m_end) ahead.load(d, next + tid, m_end);
@@ -736,7 +740,7 @@ __device__ inline void spread_block(const Dev& d, int sblk, int collide, int64_t
       d.F[2 * d.pstride + base] = az;
       if (collide) {
         const Nbr o = neighbours(x, y, z, B.nx, B.ny, B.nz);
-        sc_finish<ST, EX == kMoments, kOff32<SZ>, false, kThrough<SZ>>(d, B, o, base, n, d.pop[(n + 1) & 1], g, B.gx + ax, B.gy + ay, B.gz + az, true,
+        sc_finish<ST, EX == kMoments, kOff32<SZ>, false, kThrough<SZ>>(d, B, o, base, n, g, B.gx + ax, B.gy + ay, B.gz + az, true,
                                                              avg, sums);
       }
     }
@@ -784,7 +788,7 @@ __device__ inline void mark_near_tiles(const Dev& d, const Bead& Bd, int b, cons
   }
 }
 
-// One workgroup per bead: bead state and terms from the patch values, the total
+// One workgroup per bead: bead state from the patch values, the total
 // force of each marker, the markers' new positions into d.pos, and the near
 // tiles of step n + 1.
 template <int NW>
@@ -814,12 +818,7 @@ __device__ inline void bead_block(const Dev& d, int b, int64_t n) {
   }
   __syncthreads();
   if (tid == 0) {
-    // folded terms are read by the spreading workgroups of this launch, and the
-    // force recorded here is to be the one they spread
-    if (d.folded)
-      sterm = d.bterms[b];
-    else
-      d.bterms[b] = sterm = step_terms(in, cen);
+    sterm = step_terms(in, cen);
     d.bstate[b].V = cen[4 * in.slot + 3] / 6.0;
   } else if (tid >= 64 && tid < 67) {
     const int a = tid - 64;
@@ -862,25 +861,6 @@ __global__ __launch_bounds__(kStepBlock, 4) void k_step_b(Dev d, int collide, in
   } else {
     step_bulk<ST, EX, SZ>(d, share + i - d.nbeads, n);
   }
-}
-
-// The terms of every bead (one workgroup per bead), for boxes with more beads
-// or patches than a spreading workgroup folds.  The only writer of d.bterms in
-// such a handle: k_step_b's workgroups all read them.
-__global__ __launch_bounds__(64) void k_step_fold(Dev d) {
-  __shared__ double cen[12];
-  const int b = blockIdx.x;
-  const TermInputs in = term_inputs(d, b);
-  if (threadIdx.x < 12) {
-    const Bead& q = d.beads[b - in.slot + threadIdx.x / 4];
-    const int k = threadIdx.x % 4;
-    double s = 0.0;
-#pragma unroll 8
-    for (int j = 0; j < q.npatch; ++j) s += patch_value(d, q.patch0 + j, k);
-    cen[threadIdx.x] = k < 3 ? s * q.inv_nv : s;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) d.bterms[b] = step_terms(in, cen);
 }
 
 // Advection of the last step of a sequence, in place, and the step counter.
@@ -984,9 +964,8 @@ void launch_step_st(const Dev& d, const StepArgs& p) {
     launch_step_w<ST, 4>(d, p);
 }
 
-StepArgs step_args(const Dev& d, int mode, int share, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
+StepArgs step_args(int mode, int share, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
   const bool second = mode == kLaunchStepB || mode == kLaunchStepSpread;
-  if (second && d.folded) hipLaunchKernelGGL(k_step_fold, dim3(d.nbeads), dim3(64), 0, s, d);
   return {second, mode == kLaunchStepA || mode == kLaunchStepB, share, s, ev0, ev1};
 }
 
@@ -1002,11 +981,11 @@ void launch_step_sto(const Dev& d, int storage, const StepArgs& p) {
 }  // namespace
 
 void launch_step(const Dev& d, int storage, int mode, int share, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1) {
-  launch_step_sto(d, storage, step_args(d, mode, share, s, ev0, ev1));
+  launch_step_sto(d, storage, step_args(mode, share, s, ev0, ev1));
 }
 
 void launch_step_mom(const Dev& d, int mode, int share, hipStream_t s) {
-  const StepArgs p = step_args(d, mode, share, s, nullptr, nullptr);
+  const StepArgs p = step_args(mode, share, s, nullptr, nullptr);
   if (d.width == 2)
     launch_step_n<kFp32, 2, kMoments>(d, p);
   else if (d.width == 3)

@@ -453,9 +453,9 @@ class Lattice:
 # workgroups of 128 / 256 / 512 nodes, block order round robin over the XCDs
 # or one contiguous range per XCD, the immersed-boundary work beside the blocks
 # (resident >= 0), or (resident -1) the serial order: that work, then one
-# full-grid launch.  Where the fused step runs (FP32 storage; one box or a batch
-# of few beads), every shape with resident >= 0 is the same launch; elsewhere
-# resident >= 1 is that many persistent workgroups per CU.
+# full-grid launch.  Where the fused step runs (FP32 storage; few beads), every
+# shape with resident >= 0 is the same launch; elsewhere resident >= 1 is that many
+# persistent workgroups per CU.
 LAUNCH_CANDIDATES = ((512, True, 0), (512, False, 0), (256, True, 0), (256, False, 0), (128, True, 0),
                      (512, False, 1), (512, True, 1), (512, False, 2), (256, False, 2), (256, False, 4),
                      (512, False, -1), (256, False, -1))

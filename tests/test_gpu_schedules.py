@@ -1,9 +1,18 @@
-"""Batches on the two-stream schedule (more than 128 beads): the persistent bulk
-launch, whose workgroups claim their blocks with FP32 storage, gives the bits of the
-other launch shapes."""
+"""FP32 handles at the edges of the rule between the fused step and the two-stream
+schedule (36 beads or 256 surface patches in a box; 128 beads in a batch), and what
+the two-stream schedule has for them alone: the persistent bulk launch that claims
+its blocks, and the recompute of the adjoint.
+
+Bars as everywhere for the coupled step: velocity rel-L2 1e-5 and element-wise
+1e-5 of max |u| (FP32 sums), markers 1e-10 lattice units per step; the adjoint's
+short horizons 2e-5 of each component."""
+import math
+
 import numpy as np
 import pytest
 
+from helpers import max_rel, oracle_from, rel_l2
+from oracle import adjoint as oracle_adjoint
 from paper_2202_12147_amd import lbmib, workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -12,10 +21,49 @@ SHAPES = [(512, False, 0), (512, False, 1), (512, True, 2), (256, False, 4), (25
           (128, False, 8), (256, False, -1)]
 
 
+def _box(count, level, width=3, rows=3):
+    """`count` swimmers in a ragged box, `rows` along x and the rows 12 apart."""
+    lines = -(-count // rows)
+    sw = [wl.swimmer((16 + 33 * (i % rows), 2 + 12 * (i // rows), 3), 10.0, level=level, T=500.0, phi0=0.3 * i)
+          for i in range(count)]
+    return dict(name=f"{count} swimmers, level {level}", shape=(33 * rows, max(29, 12 * lines + 3), 29), tau=1.0,
+                forcing=wl.GUO, width=width, swimmers=sw)
+
+
+@pytest.mark.parametrize("count,level", [(4, 3), (5, 3), (2, 4), (12, 1), (13, 1), (22, 0)])
+@pytest.mark.parametrize("storage", [lbmib.FP32_SHIFTED, lbmib.FP32_INPLACE])
+def test_edges_match_oracle(count, level, storage):
+    # 252 | 315 and 486 patches; 36 | 39 and 66 beads
+    case = _box(count, level)
+    print(case["name"], case["shape"], "storage", storage, flush=True)
+    lat, o = lbmib.from_workload(case, storage=storage), oracle_from(case)
+    lat.step(2)
+    lat.step(4)
+    o.step(6)
+    u, ref = lat.velocity(), o.velocity()
+    assert rel_l2(u, ref) < 1e-5 and max_rel(u, ref) < 1e-5
+    assert np.abs(lat.markers() - o.markers()).max() < 1e-10 * 6
+
+
 def _same(a, b, what):
     assert np.array_equal(a.markers(), b.markers()), what
     assert np.array_equal(a.marker_forces(), b.marker_forces()), what
     assert np.array_equal(a.populations(), b.populations()), what
+
+
+@pytest.mark.parametrize("storage", [lbmib.FP32_SHIFTED, lbmib.FP32_INPLACE])
+def test_launch_shapes_of_a_two_stream_box(storage):
+    case = _box(22, 0)
+    ref = lbmib.from_workload(case, storage=storage)
+    ref.step(41)
+    for shape in SHAPES:
+        for graphs in (True, False):
+            print("shape", shape, "graphs", graphs, flush=True)
+            lat = lbmib.from_workload(case, storage=storage, use_graphs=graphs)
+            lat.set_stream_collide_launch(*shape)
+            lat.step(9)
+            lat.step(32)
+            _same(lat, ref, (shape, graphs))
 
 
 def test_launch_shapes_of_a_large_batch():
@@ -35,3 +83,19 @@ def test_launch_shapes_of_a_large_batch():
         lat.step(9)
         lat.step(32)
         _same(lat, ref, shape)
+
+
+def test_adjoint_on_the_two_stream_schedule():
+    case = wl.adjoint_case(reduced=True)
+    case["swimmers"] = [wl.swimmer((12.0, 12.0, 12.0), 7.0, level=5, A=1e-3, T=2000.0, alpha=math.pi / 3)]
+    print("level 5", flush=True)
+    got = [lbmib.from_workload(case, use_graphs=g).adjoint(20, checkpoint=8) for g in (True, False)]
+    assert got[0][0] == got[1][0] and np.array_equal(got[0][1], got[1][1])
+    J, g = got[0]
+    Jo, go = oracle_adjoint.displacement_gradient(case, 20, checkpoint_every=0)
+    print(J, Jo, g, go, flush=True)
+    assert abs(J - Jo) <= 2e-5 * abs(Jo)
+    assert np.all(np.abs(g - go) <= 2e-5 * np.abs(go)), (g, go)
+    # the segments' recompute repeats the forward run: one segment gives the same bits
+    J1, g1 = lbmib.from_workload(case).adjoint(20, checkpoint=20)
+    assert J1 == J and np.array_equal(g1, g)
