@@ -353,7 +353,8 @@ int lbm_kernel_time(lbm_handle* h, double* ms, int64_t* launches);
  * `resident` workgroups per compute unit that walk the blocks (FP16) or claim
  * them one by one (FP32).  These are FP16 storage, boxes of more than 36 beads or
  * 256 surface patches (a bead of v mesh nodes has v / 32, rounded up), and batches
- * of more than 64 beads (128 where the population sets take at most 1 GiB).
+ * of more than 64 beads (128 where the population sets take at most 1 GiB; 30
+ * where a box has more than 512 mesh nodes).
  * Results are bitwise identical for every choice.  Errors: LBM_EINVAL. */
 int lbm_set_stream_collide_launch(lbm_handle* h, int block, int xcd_remap, int resident);
 /* Algorithmic bytes one stream-collide launch moves (19 populations read and

@@ -273,20 +273,33 @@ void set_near_bounds(lbm_handle* h) {
 //    twice.  Up to kWriteThroughBytes of populations: 24 boxes, 1.7 M nodes 127 us
 //    per step against 106 fused; 32 boxes, 5.6 M 297 and 271; 40 boxes, 6.7 M 358
 //    and 344; 60 boxes, 6.6 M 259 and 291.  Beyond: 16 boxes 254 and 237; 32 boxes,
-//    11.8 M 441 and 522; 40 boxes, 7.5 M 323 and 361.
-constexpr int kFusedBoxBeads = 36, kFusedBatchBeads = 64, kFusedBatchBeadsSmall = 128;
+//    11.8 M 441 and 522; 40 boxes, 7.5 M 323 and 361.  Boxes of more markers than a
+//    spreading workgroup holds at once make longer slabs, and the line lies lower.
+//    96x48x48 with a swimmer of 642-node beads: 8 boxes 112 and 100, 12 boxes 130
+//    and 149, 21 boxes 208 and 274; 64^3 with two of 162-node beads: 4 boxes 63 and
+//    46, 6 boxes 68 and 64, 8 boxes 76 and 84, 16 boxes 160 and 173; 96^3 with four:
+//    2 boxes 86 and 68, 3 boxes 90 and 94, 4 boxes 115 and 127.
+constexpr int kFusedBoxBeads = 36, kFusedBatchBeads = 64, kFusedBatchBeadsSmall = 128, kFusedBatchBeadsLong = 30;
 static_assert(kFusedBoxBeads <= kFoldBeads, "the beads of a box fit its spreading workgroups' tables");
 bool choose_two_stream(const lbm_handle* h) {
   if (h->swimmers.empty()) return false;
-  const int most = h->dev.small_pops ? kFusedBatchBeadsSmall : kFusedBatchBeads;
-  if (h->storage == LBM_FP16_SHIFTED || (h->boxes.size() > 1 && h->beads.size() > (size_t)most)) return true;
-  std::vector<int> beads(h->boxes.size()), patches(h->boxes.size());
+  if (h->storage == LBM_FP16_SHIFTED) return true;
+  struct Count {
+    int beads = 0, patches = 0, markers = 0;
+  };
+  std::vector<Count> box(h->boxes.size());
+  Count most;
   for (const Bead& b : h->beads) {
-    beads[b.box] += 1;
-    patches[b.box] += (b.nv + kPatchOwn - 1) / kPatchOwn;
+    Count& c = box[b.box];
+    most.beads = std::max(most.beads, ++c.beads);
+    most.patches = std::max(most.patches, c.patches += (b.nv + kPatchOwn - 1) / kPatchOwn);
+    most.markers = std::max(most.markers, c.markers += b.nv);
   }
-  return *std::max_element(beads.begin(), beads.end()) > kFusedBoxBeads ||
-         *std::max_element(patches.begin(), patches.end()) > kFoldPatches;
+  if (most.beads > kFusedBoxBeads || most.patches > kFoldPatches) return true;
+  if (h->boxes.size() == 1) return false;
+  int line = h->dev.small_pops ? kFusedBatchBeadsSmall : kFusedBatchBeads;
+  if (most.markers > kStepBlock) line = kFusedBatchBeadsLong;
+  return (int)h->beads.size() > line;
 }
 
 bool two_stream(const lbm_handle* h) { return h->two; }

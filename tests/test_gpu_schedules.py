@@ -1,7 +1,7 @@
 """FP32 handles at the edges of the rule between the fused step and the two-stream
-schedule (36 beads or 256 surface patches in a box; 128 beads in a batch), and what
-the two-stream schedule has for them alone: the persistent bulk launch that claims
-its blocks, and the recompute of the adjoint.
+schedule (36 beads or 256 surface patches in a box; 128 beads in a batch, 30 where a
+box holds more than 512 markers), and what the two-stream schedule has for them alone:
+the persistent bulk launch that claims its blocks, and the recompute of the adjoint.
 
 Bars as everywhere for the coupled step: velocity rel-L2 1e-5 and element-wise
 1e-5 of max |u| (FP32 sums), markers 1e-10 lattice units per step; the adjoint's
@@ -83,6 +83,29 @@ def test_launch_shapes_of_a_large_batch():
         lat.step(9)
         lat.step(32)
         _same(lat, ref, shape)
+
+
+@pytest.mark.parametrize("boxes,bitwise", [(5, True), (6, False)])
+def test_batch_of_boxes_with_many_markers(boxes, bitwise):
+    # two swimmers of 162-node beads per box: 972 markers; 30 | 36 beads.  On the
+    # fused step a box gives the bits it gives alone
+    cases = []
+    for i in range(boxes):
+        c = _box(2, 2, rows=1)
+        cases.append(dict(c, shape=(34 + i, 30, 31), tau=1.0 - 0.02 * i))
+    print("boxes", boxes, flush=True)
+    batch = lbmib.batch_from_ensemble(dict(boxes=cases))
+    batch.step(12)
+    m = batch.markers().reshape(boxes, -1, 3)
+    for i in (0, boxes - 1):
+        one = lbmib.batch_from_ensemble(dict(boxes=cases[i:i + 1]))
+        one.step(12)
+        if bitwise:
+            assert np.array_equal(batch.velocity(i), one.velocity(0))
+            assert np.array_equal(m[i], one.markers())
+        else:
+            assert rel_l2(batch.velocity(i), one.velocity(0)) < 1e-5
+            assert np.abs(m[i] - one.markers()).max() < 1e-10 * 12
 
 
 def test_adjoint_on_the_two_stream_schedule():
