@@ -1,7 +1,9 @@
 """lbm_step's bookkeeping on the host, against the HIP stand-in of
-tests/hoststub (no GPU, no kernel runs): a call that is refused because the
-caller captures the stream leaves nothing marked as done, and a call that fails
-half way counts exactly the steps that were enqueued."""
+tests/hoststub (no GPU, no kernel runs), built with AddressSanitizer and
+UndefinedBehaviorSanitizer: a call that is refused because the caller captures the
+stream leaves nothing marked as done, a call that fails half way counts exactly the
+steps that were enqueued, and graphs captured late are dropped and captured again
+where the launches change."""
 import ctypes as C
 import os
 import subprocess
@@ -15,6 +17,11 @@ WRAPPED = ["hipStreamBeginCapture", "hipStreamEndCapture", "hipGraphInstantiate"
            "_ZN5lbmib17launch_bead_statsERKNS_3DevEiP12ihipStream_t",
            "_ZN5lbmib21launch_interp_advanceERKNS_3DevEP12ihipStream_t"]
 
+def _asan_runtime():
+    return subprocess.run([CLANG, "-print-file-name=libclang_rt.asan-x86_64.so"], capture_output=True,
+                          text=True).stdout.strip()
+
+
 pytestmark = pytest.mark.skipif(not os.path.exists(CLANG), reason="needs the ROCm clang++")
 
 
@@ -24,7 +31,8 @@ def stub(tmp_path_factory):
     csrc = os.path.join(ROOT, "paper_2202_12147_amd", "csrc")
     here = os.path.join(ROOT, "tests", "hoststub")
     subprocess.run([CLANG, "-x", "c++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-D__HIP_MEMORY_SCOPE_SYSTEM=5",
-                    "-I/opt/rocm/include", "-I" + os.path.join(ROOT, "include"), "-O1", "-fPIC", "-shared",
+                    "-I/opt/rocm/include", "-I" + os.path.join(ROOT, "include"), "-g", "-O1", "-fPIC", "-shared",
+                    "-D_GLIBCXX_ASSERTIONS", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
                     os.path.join(csrc, "runtime.cpp"), os.path.join(csrc, "adjoint.cpp"),
                     os.path.join(here, "hip_stub.cpp"), os.path.join(here, "step_control.cpp"), "-o", lib]
                    + ["-Wl,--wrap=" + w for w in WRAPPED], check=True)
@@ -57,7 +65,8 @@ case = wl.small_case()
 def handle(**kw):
     return lbmib.from_workload(case, **kw)
 """
-    r = subprocess.run([sys.executable, "-c", prelude + body], capture_output=True, text=True, timeout=300)
+    env = dict(os.environ, LD_PRELOAD=_asan_runtime(), ASAN_OPTIONS="detect_leaks=0:abort_on_error=1")
+    r = subprocess.run([sys.executable, "-c", prelude + body], capture_output=True, text=True, timeout=300, env=env)
     assert r.returncode == 0, r.stdout + r.stderr
 
 
@@ -116,4 +125,36 @@ control(fail_launch=2)
 refused(lat.step, 320)
 r = records()
 assert lat.time == r[1] + r[2] < 960
+""")
+
+
+@pytest.mark.parametrize("swimmers", [True, False])
+def test_graphs_across_changes_of_the_launches(stub, swimmers):
+    _run(stub, f"""
+if not {swimmers}:
+    case = dict(case, swimmers=[])
+lat = handle()
+def run(first, calls):
+    before = records()[3]
+    for n in calls[:first]:
+        lat.step(n)
+    assert records()[3] == before       # launched directly
+    for n in calls[first:]:
+        lat.step(n)
+    assert records()[3] > before        # replayed
+calls = [1, 300, 211, 640, 33, 7]
+run(3, calls)
+lat.average_begin(3)
+run(3, calls)
+lat.set_stream_collide_launch(128, True, -1)
+run(3, calls)
+lat.average_begin(0)
+lat.set_kernel_timing(True)
+lat.step(40)
+lat.set_kernel_timing(False)
+run(3, calls)
+lat.adjoint(1, checkpoint=1) if {swimmers} else None
+lat.step(64)
+assert lat.time == 4 * sum(calls) + 104 + ({swimmers} is True)
+lat.close()
 """)
