@@ -75,6 +75,8 @@ struct lbm_handle {
   // device buffers
   void* pop[2] = {nullptr, nullptr};
   float *F = nullptr, *u = nullptr, *uout = nullptr;
+  double* px_buf = nullptr;       // exchange of populations (allocated on first use)
+  int64_t px_size = 0;            // its values
   double* avg_sums = nullptr;     // time-average sums [3][pstride] (allocated on first use)
   int* stamp = nullptr;
   Box* d_boxes = nullptr;

@@ -1638,29 +1638,33 @@ int lbm_batch_get_conserved_noalloc(lbm_handle* h, int32_t box, int32_t parts, d
 
 // Populations between the host array (box after box, each [19][nz][ny][nx]) and
 // the device, through a device buffer of at most kExchange values (fewer, down
-// to kExchangeMin, where device memory is short).
+// to kExchangeMin, where device memory is short).  The handle keeps the buffer: a
+// free waits for all work on the device, other handles' included.  Where there is
+// no memory for it, or not more than kHostExchange values to convert, the host
+// converts.  At that bound the host is the slower by 10 to 30 us of 100 (19^3
+// nodes, 130 k values: set 108 us on the host and 95 through the buffer, get 112
+// and 76); the smallest box, 16^3, has 78 k values.
 static int exchange_populations(lbm_handle* h, double* host, bool set) {
-  constexpr int64_t kExchange = int64_t(1) << 23, kExchangeMin = int64_t(1) << 16;  // 64 MiB, 512 KiB
-  // Up to kHostExchange values the host converts: there the two cost about the same
-  // (19^3 nodes, 130 k values: set 108 us on the host and 95 through the buffer, get
-  // 112 and 76; 97x65x131: get 38 and 12 ms), and no device memory is needed.
+  constexpr int64_t kExchange = int64_t(1) << 20, kExchangeMin = int64_t(1) << 16;  // 8 MiB, 512 KiB
   constexpr int64_t kHostExchange = int64_t(1) << 17;
   const int64_t total = kQ * h->nodes;
-  if (total <= kHostExchange)
+  if (total > kHostExchange && !h->px_buf)
+    for (h->px_size = std::min(total, kExchange); h->px_size >= kExchangeMin; h->px_size /= 2) {
+      int rc = LBM_OK;
+      h->px_buf = h->alloc<double>((size_t)h->px_size, rc);
+      if (!rc) break;
+      (void)hipGetLastError();  // not the next launch's
+    }
+  if (total <= kHostExchange || !h->px_buf)
     return h->storage == LBM_FP16_SHIFTED ? host_populations<_Float16>(h, host, set)
                                           : host_populations<float>(h, host, set);
   Dev d = h->dev;
+  d.px_buf = h->px_buf;
   d.px_set = set ? 1 : 0;
-  int64_t chunk = std::min(total, kExchange);
-  while (hipMalloc(reinterpret_cast<void**>(&d.px_buf), sizeof(double) * chunk) != hipSuccess) {
-    (void)hipGetLastError();
-    if (chunk <= kExchangeMin) return h->fail(LBM_ENOMEM, "population exchange buffer allocation failed");
-    chunk /= 2;
-  }
   int rc = LBM_OK;
-  for (int64_t from = 0; from < total && !rc; from += chunk) {
+  for (int64_t from = 0; from < total && !rc; from += h->px_size) {
     d.px_from = from;
-    d.px_count = std::min(chunk, total - from);
+    d.px_count = std::min(h->px_size, total - from);
     const size_t bytes = sizeof(double) * d.px_count;
     if (set) rc = h->hip(hipMemcpyAsync(d.px_buf, host + from, bytes, hipMemcpyHostToDevice, h->stream), "hipMemcpyAsync");
     if (!rc) launch_velocity(d, h->storage, 0, nullptr, nullptr, h->stream);
@@ -1669,7 +1673,6 @@ static int exchange_populations(lbm_handle* h, double* host, bool set) {
       rc = h->hip(hipMemcpyAsync(host + from, d.px_buf, bytes, hipMemcpyDeviceToHost, h->stream), "hipMemcpyAsync");
     if (!rc) rc = h->hip(hipStreamSynchronize(h->stream), "hipStreamSynchronize");
   }
-  (void)hipFree(d.px_buf);
   return rc;
 }
 

@@ -1,6 +1,6 @@
 // Beside hip_stub.cpp, for tests/test_host_step.py: a stream under capture by
-// the caller, a graph that cannot be instantiated, and records of what lbm_step
-// enqueued (linked with --wrap for the functions hip_stub.cpp defines).
+// the caller, a graph that cannot be instantiated, device memory that is short, and
+// records of what lbm_step enqueued (linked with --wrap for the functions hip_stub.cpp defines).
 #include <hip/hip_runtime.h>
 
 #include "../../paper_2202_12147_amd/csrc/common.h"
@@ -12,6 +12,8 @@ int g_capturing = 0;        // the caller captures the stream
 int g_fail_instantiate = 0; // graphs cannot be instantiated
 bool g_own = false;         // inside a capture of the library's own
 int g_fail_launch = -1;     // graph launches that still succeed; -1: all
+size_t g_malloc_limit = ~size_t(0);  // larger device allocations fail
+long g_mallocs = 0, g_frees = 0;
 long g_marks = 0, g_steps = 0, g_graph_steps = 0, g_launched = 0;
 }  // namespace
 
@@ -20,6 +22,11 @@ void control(int capturing, int fail_instantiate, int fail_launch) {
   g_capturing = capturing;
   g_fail_instantiate = fail_instantiate;
   g_fail_launch = fail_launch;
+}
+void limit_malloc(size_t bytes) { g_malloc_limit = bytes; }
+void allocations(long out[2]) {
+  out[0] = g_mallocs;
+  out[1] = g_frees;
 }
 // Prologue marks launched, steps whose closing launch was made directly, steps
 // replayed from graphs; graph launches.
@@ -35,6 +42,17 @@ hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* st) {
   return hipSuccess;
 }
 
+hipError_t __real_hipMalloc(void** p, size_t n);
+hipError_t __wrap_hipMalloc(void** p, size_t n) {
+  if (n > g_malloc_limit) return hipErrorOutOfMemory;
+  ++g_mallocs;
+  return __real_hipMalloc(p, n);
+}
+hipError_t __real_hipFree(void* p);
+hipError_t __wrap_hipFree(void* p) {
+  ++g_frees;
+  return __real_hipFree(p);
+}
 hipError_t __real_hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode m);
 hipError_t __wrap_hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode m) {
   g_own = true;

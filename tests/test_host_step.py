@@ -1,9 +1,9 @@
-"""lbm_step's bookkeeping on the host, against the HIP stand-in of
+"""Bookkeeping of the host code, against the HIP stand-in of
 tests/hoststub (no GPU, no kernel runs), built with AddressSanitizer and
 UndefinedBehaviorSanitizer: a call that is refused because the caller captures the
 stream leaves nothing marked as done, a call that fails half way counts exactly the
-steps that were enqueued, and graphs captured late are dropped and captured again
-where the launches change."""
+steps that were enqueued, graphs captured late are dropped and captured again where
+the launches change, and populations are exchanged where device memory is short."""
 import ctypes as C
 import os
 import subprocess
@@ -13,7 +13,7 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CLANG = "/opt/rocm/llvm/bin/clang++"
-WRAPPED = ["hipStreamBeginCapture", "hipStreamEndCapture", "hipGraphInstantiate", "hipGraphLaunch",
+WRAPPED = ["hipMalloc", "hipFree", "hipStreamBeginCapture", "hipStreamEndCapture", "hipGraphInstantiate", "hipGraphLaunch",
            "_ZN5lbmib17launch_bead_statsERKNS_3DevEiP12ihipStream_t",
            "_ZN5lbmib21launch_interp_advanceERKNS_3DevEP12ihipStream_t"]
 
@@ -53,6 +53,11 @@ def control(capturing=0, fail_instantiate=0, fail_launch=-1):
 def records():
     out = (C.c_long * 4)()
     lib.records(out)
+    return list(out)
+lib.limit_malloc.argtypes = [C.c_size_t]
+def allocations():
+    out = (C.c_long * 2)()
+    lib.allocations(out)
     return list(out)
 def refused(f, *a):
     try:
@@ -157,4 +162,36 @@ lat.adjoint(1, checkpoint=1) if {swimmers} else None
 lat.step(64)
 assert lat.time == 4 * sum(calls) + 104 + ({swimmers} is True)
 lat.close()
+""")
+
+
+@pytest.mark.parametrize("storage,scale", [(0, 1.0), (1, 2.0 ** 20), (2, 1.0), (3, 1.0)])
+def test_populations_without_device_memory(stub, storage, scale):
+    # the host converts: what is set comes back as the storage rounds it
+    _run(stub, f"""
+import numpy as np
+lat = lbmib.Lattice((33, 24, 35), 0.9, storage={storage}, fp16_scale={scale})
+g = 1e-3 * np.random.default_rng(0).standard_normal((19, 35, 24, 33))
+lib.limit_malloc(1 << 10)
+lat.set_populations(g)
+got = lat.populations()
+assert np.abs(got - g).max() < {2e-6 if storage == 1 else 1e-7} and got.any()
+""")
+
+
+def test_exchange_keeps_its_buffer(stub):
+    # a free waits for the whole device: none, and no allocation, after the first call
+    _run(stub, """
+import numpy as np
+lat = lbmib.Lattice((64, 40, 32), 0.9)
+g = np.zeros((19, 32, 40, 64))
+lat.set_populations(g)
+before = allocations()
+for _ in range(3):
+    lat.set_populations(g)
+    lat.populations()
+assert allocations() == before
+n = before[0] - before[1]
+lat.close()
+assert allocations()[1] - before[1] == n   # destroyed with the handle
 """)
