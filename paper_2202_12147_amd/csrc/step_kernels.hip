@@ -915,11 +915,16 @@ void launch_ev(K kernel, int grid, int lds, hipStream_t s, hipEvent_t ev0, hipEv
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(kStepBlock), lds, s, args...);
 }
 
-// Unused LDS that k_step_a is launched with, so that two of its workgroups fit a
-// compute unit as of k_step_b (128 registers): 16 wavefronts stream faster than
-// 24 (1024x256x256 1803 us per step with three, 1747 with two; 128^3 in place
-// 53.8 and 53.4; one of k_step_b's per unit: 60.3).
-constexpr int kStepALds = 16384;
+// k_step_a is launched with unused LDS up to a total of kStepALds, so that two of its
+// workgroups fit a compute unit as of k_step_b (128 registers) and a third does not,
+// whatever its kernel width needs: 16 wavefronts stream faster than 24 (1024x256x256
+// 1803 us per step with three, 1747 with two; 128^3 in place 53.8 and 53.4; width 2
+// 1742 and 1699, 56.2 and 53.3; one of k_step_b's per unit: 60.3).
+constexpr int kStepALds = 57344;
+template <int NW>
+constexpr int kPatchLds = kPatchLocal * (3 * (int)sizeof(double) + 3 * NW * (int)(sizeof(float) + sizeof(int)) + (int)sizeof(int)) +
+                          3 * (int)sizeof(float) * (3 * kPatchTri + kPatchTri + 4 * kPatchHinge);
+static_assert(3 * kStepALds > 160 * 1024 && kPatchLds<4> < kStepALds, "two workgroups per compute unit, not three");
 
 struct StepArgs {
   int b, x, y;  // launch (0: a, 1: b) and its two integer arguments
@@ -930,7 +935,7 @@ struct StepArgs {
 template <int ST, int NW, int EX, int SZ>
 void launch_step_i(const Dev& d, const StepArgs& p) {
   if (p.b == 0)
-    launch_ev(k_step_a<ST, NW, EX, SZ>, d.npatch + d.nboxes + p.y, kStepALds, p.s, p.ev0, p.ev1, d, p.x, d.npatch + d.nboxes);
+    launch_ev(k_step_a<ST, NW, EX, SZ>, d.npatch + d.nboxes + p.y, kStepALds - kPatchLds<NW>, p.s, p.ev0, p.ev1, d, p.x, d.npatch + d.nboxes);
   else
     launch_ev(k_step_b<ST, NW, EX, SZ>, d.step_spread_blocks + d.nbeads + (p.x ? d.nstep - p.y : 0), 0, p.s, p.ev0,
               p.ev1, d, p.x, p.y);
