@@ -554,6 +554,7 @@ __device__ inline void spread_block(const Dev& d, int sblk, int collide, int64_t
   __shared__ StepEntry ent[kStepBlock];
   __shared__ float acc[kWaves][3][64];
   __shared__ int wave_cnt[kWaves];
+  __shared__ int nonfinite;  // the chunk has a force or a position that is not finite
   __shared__ BeadTerms terms[kFoldBeads];
   __shared__ double fv[kFoldBeads * 4];
   static_assert(sizeof(ent) >= sizeof(double) * 4 * kFoldPatches, "patch values fit the entries' LDS");
@@ -663,6 +664,7 @@ __device__ inline void spread_block(const Dev& d, int sblk, int collide, int64_t
       const int before = __popcll(mask & ((1ull << lane) - 1ull));
       __syncthreads();  // previous chunk's entries fully consumed, bead terms made
       if (lane == 0) wave_cnt[wave] = __popcll(mask);
+      if (tid == 0) nonfinite = 0;
       __syncthreads();
       int at = before, total = 0;
       for (int w = 0; w < kWaves; ++w) {
@@ -688,23 +690,31 @@ __device__ inline void spread_block(const Dev& d, int sblk, int collide, int64_t
         const float fx = total_force(q.fm[0], q.gv[0], t.pv, t.share[0]),
                     fy = total_force(q.fm[1], q.gv[1], t.pv, t.share[1]),
                     fz = total_force(q.fm[2], q.gv[2], t.pv, t.share[2]);
+        // a sum that is not finite has a term that is not
+        if (!(fabsf(fx + fy + fz + (float)(q.x[0] + q.x[1] + q.x[2])) < INFINITY)) nonfinite = 1;
 #pragma unroll
         for (int l = 0; l < kSlabLayers; ++l) {
           float wz = 0.0f;
 #pragma unroll
           for (int k = 0; k < NW; ++k) wz = l - off[2] == k ? w[2][k] : wz;
-          *reinterpret_cast<float4*>(E.f[l]) = make_float4(wz * fx, wz * fy, wz * fz, 0.0f);
+          *reinterpret_cast<float4*>(E.f[l]) =
+              wz != 0.0f ? make_float4(wz * fx, wz * fy, wz * fz, 0.0f) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         }
       }
       __syncthreads();
-#pragma unroll 4
-      for (int e = subset; e < total; e += kSubsets) {
-        const StepEntry& E = ent[e];
+      auto add = [&](const StepEntry& E) {
         const float w = E.wx[lane % kTile] * E.wy[lane / kTile];
         const float4 f = *reinterpret_cast<const float4*>(E.f[layer]);
         sx = fmaf(w, f.x, sx);
         sy = fmaf(w, f.y, sy);
         sz = fmaf(w, f.z, sz);
+      };
+      if (!nonfinite) {
+#pragma unroll 4
+        for (int e = subset; e < total; e += kSubsets) add(ent[e]);
+      } else {  // not beyond the stencils, where the weights are zero
+        for (int e = subset; e < total; e += kSubsets)
+          if (ent[e].wx[lane % kTile] != 0.0f && ent[e].wy[lane / kTile] != 0.0f) add(ent[e]);
       }
     };
     // the box's markers from the first covering bead's on, kStepBlock at a
