@@ -1,7 +1,8 @@
 """FP32 handles at the edges of the rule between the fused step and the two-stream
-schedule (36 beads or 256 surface patches in a box; 128 beads in a batch, 30 where a
-box holds more than 512 markers), and what the two-stream schedule has for them alone:
-the persistent bulk launch that claims its blocks, and the recompute of the adjoint.
+schedule (36 beads or 256 surface patches in a box; 128 beads in a batch, 64 beyond 1
+GiB of populations, 30 where a box holds more than 512 markers), and what the two-stream
+schedule has for them alone: the persistent bulk launch that claims its blocks, and the
+recompute of the adjoint.
 
 Bars as everywhere for the coupled step: velocity rel-L2 1e-5 and element-wise
 1e-5 of max |u| (FP32 sums), markers 1e-10 lattice units per step; the adjoint's
@@ -43,6 +44,19 @@ def test_edges_match_oracle(count, level, storage):
     u, ref = lat.velocity(), o.velocity()
     assert rel_l2(u, ref) < 1e-5 and max_rel(u, ref) < 1e-5
     assert np.abs(lat.markers() - o.markers()).max() < 1e-10 * 6
+
+
+@pytest.mark.parametrize("storage,shape", [(lbmib.FP32_SHIFTED, (200, 197, 181)), (lbmib.FP32_INPLACE, (243, 241, 244))])
+def test_populations_beyond_the_write_through_bound(storage, shape):
+    # more than 1 GiB of populations (other loads and stores), each set below 4 GiB
+    case = dict(wl.small_case(), shape=shape, swimmers=[wl.swimmer((6, 2, 90), 10.0, T=500.0)])
+    print(shape, "storage", storage, flush=True)
+    lat, o = lbmib.from_workload(case, storage=storage), oracle_from(case)
+    lat.step(3)
+    o.step(3)
+    u, ref = lat.velocity(), o.velocity()
+    assert rel_l2(u, ref) < 1e-5 and max_rel(u, ref) < 1e-5
+    assert np.abs(lat.markers() - o.markers()).max() < 1e-10 * 3
 
 
 def _same(a, b, what):
@@ -106,6 +120,31 @@ def test_batch_of_boxes_with_many_markers(boxes, bitwise):
         else:
             assert rel_l2(batch.velocity(i), one.velocity(0)) < 1e-5
             assert np.abs(m[i] - one.markers()).max() < 1e-10 * 12
+
+
+@pytest.mark.parametrize("boxes,bitwise", [(21, True), (22, False)])
+def test_batch_beyond_the_write_through_bound(boxes, bitwise):
+    # more than 1 GiB of populations; 63 | 66 beads
+    ens = wl.ensemble(seed=3, nboxes=boxes)
+    for i, b in enumerate(ens["boxes"]):
+        b["shape"] = (72 - i % 3, 71 + i % 2, 70)
+        mid = np.array([s // 2 for s in b["shape"]], float)
+        b["swimmers"][0]["centres"] = np.stack([mid - (10.0, 0, 0), mid, mid + (10.0, 0, 0)])
+        b["swimmers"][0]["L0"] = np.array([10.0, 10.0])
+    assert 2 * 19 * 4 * sum(int(np.prod(b["shape"])) for b in ens["boxes"]) > 1 << 30
+    print("boxes", boxes, flush=True)
+    batch = lbmib.batch_from_ensemble(ens)
+    batch.step(6)
+    m = batch.markers().reshape(boxes, -1, 3)
+    for i in (0, boxes - 1):
+        one = lbmib.batch_from_ensemble(dict(ens, boxes=ens["boxes"][i:i + 1]))
+        one.step(6)
+        if bitwise:
+            assert np.array_equal(batch.velocity(i), one.velocity(0))
+            assert np.array_equal(m[i], one.markers())
+        else:
+            assert rel_l2(batch.velocity(i), one.velocity(0)) < 1e-5
+            assert np.abs(m[i] - one.markers()).max() < 1e-10 * 6
 
 
 def test_adjoint_on_the_two_stream_schedule():

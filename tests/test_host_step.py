@@ -195,3 +195,31 @@ n = before[0] - before[1]
 lat.close()
 assert allocations()[1] - before[1] == n   # destroyed with the handle
 """)
+
+
+def test_two_stream_box(stub, tmp_path):
+    # an FP32 box of more beads than the fused step takes: its buffers, graphs, launch
+    # shapes, checkpoints and the adjoint's recompute on two streams
+    _run(stub, f"""
+sw = [wl.swimmer((16 + 33 * (i % 3), 2 + 12 * (i // 3), 3), 10.0, level=0, T=500.0) for i in range(13)]
+case = dict(case, shape=(99, 63, 29), swimmers=sw)
+for graphs in (True, False):
+    lat = handle(use_graphs=graphs)
+    lat.step(7)
+    lat.step(70)
+    for shape in ((128, True, 3), (512, False, 1), (256, False, -1), (256, True, 0)):
+        lat.set_stream_collide_launch(*shape)
+        lat.step(40)
+    lat.average_begin(2)
+    lat.step(33)
+    lat.average_begin(0)
+    for steps, checkpoint in ((1, 4), (40, 16), (90, 20)):
+        lat.adjoint(steps, checkpoint=checkpoint, swimmer=12, rewind=steps == 40)
+    lat.save({str(tmp_path / "ck.bin")!r})
+    lat.step(3)
+    lat.load({str(tmp_path / "ck.bin")!r})
+    lat.step(3)
+    lat.markers()
+    lat.swimmer_centres()
+    lat.close()
+""")
