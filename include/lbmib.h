@@ -338,7 +338,11 @@ int lbm_load(lbm_handle* h, const char* path);
 /* ---- measurement ------------------------------------------------------------ */
 /* When on, lbm_step runs without graphs and brackets every stream-collide
  * launch with HIP events on the handle's stream; lbm_kernel_time returns the
- * summed kernel time (ms) and launch count since timing was switched on. */
+ * summed kernel time (ms) and launch count since timing was switched on.  A step
+ * without swimmers, and one in the serial order, is one launch, of stream-collide
+ * alone.  On the fused step it is two, which also hold the interpolation, membrane
+ * forces, spreading and bead statistics; on two streams it is two, whose times
+ * overlap (all blocks away from the swimmers, and those near them). */
 int lbm_set_kernel_timing(lbm_handle* h, int on);
 int lbm_kernel_time(lbm_handle* h, double* ms, int64_t* launches);
 /* Launch shape of the stream-collide kernel without swimmers and in the serial

@@ -864,9 +864,8 @@ void enqueue_two_stream(lbm_handle* h, int64_t count) {
 // Blocks of the walk that the first launch of a fused step takes: 7/16 of them,
 // a little under half, because the second launch's own work (spreading) is the
 // longer.  Measured at 1/4, 3/8, 7/16, 1/2: 128^3 in place 55.2, 53.9, 53.9,
-// 53.8 us per step, FP16 44, 42.1, 41.0, 40.1; 96^3 34.1, 33.2, 33.8, 34.5;
-// 256x128x128 110.5, 109.7, 109.7, 110.4; none or all in it cost 10 us and more
-// at 128^3.
+// 53.8 us per step; 96^3 34.1, 33.2, 33.8, 34.5; 256x128x128 110.5, 109.7, 109.7,
+// 110.4; none or all in it cost 10 us and more at 128^3.
 int step_share(const lbm_handle* h) { return h->dev.nstep / 16 * 7; }
 
 // Enqueue `count` steps on the handle's stream.  Without swimmers each step is
