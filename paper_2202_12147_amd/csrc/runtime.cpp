@@ -1638,15 +1638,15 @@ int lbm_batch_get_conserved_noalloc(lbm_handle* h, int32_t box, int32_t parts, d
 // Populations between the host array (box after box, each [19][nz][ny][nx]) and
 // the device, through a device buffer of at most kExchange values (fewer, down
 // to kExchangeMin, where device memory is short).  The handle keeps the buffer: a
-// free waits for all work on the device, other handles' included.  Pieces of 16 MiB,
-// ordered by the stream, cost what 64 MiB did (97x65x131: set 4.3 ms, get 7.3; with
-// 8 MiB and a wait after each 4.9 and 7.4).  Where there is
+// free waits for all work on the device, other handles' included.  97x65x131, 20
+// steps and the state into new host memory, ms per pass with pieces of 8, 16, 32
+// and 64 MiB: 13.7, 13.6, 13.45, 13.4 (the copy of 125 MB alone: 12.2).  Where there is
 // no memory for it, or not more than kHostExchange values to convert, the host
 // converts.  At that bound the host is the slower by 10 to 30 us of 100 (19^3
 // nodes, 130 k values: set 108 us on the host and 95 through the buffer, get 112
 // and 76); the smallest box, 16^3, has 78 k values.
 static int exchange_populations(lbm_handle* h, double* host, bool set) {
-  constexpr int64_t kExchange = int64_t(1) << 21, kExchangeMin = int64_t(1) << 16;  // 16 MiB, 512 KiB
+  constexpr int64_t kExchange = int64_t(1) << 22, kExchangeMin = int64_t(1) << 16;  // 32 MiB, 512 KiB
   constexpr int64_t kHostExchange = int64_t(1) << 17;
   const int64_t total = kQ * h->nodes;
   if (total > kHostExchange && !h->px_buf)
