@@ -22,7 +22,7 @@ if ROOT not in sys.path:
 PEAK_HBM_GBS = 8000.0
 # stream-collide launch shapes (block, XCD remap, resident) of the workloads.
 # Single FP32 boxes with swimmers run the fused step, whatever the shape, for
-# resident >= 0; the shape matters with FP16 storage and for large batches.  The
+# resident >= 0; the shape matters with FP16 storage, many beads and large batches.  The
 # batch section runs the launch tuner (lbmib.tune_launch) and times the shape it
 # picks; BATCH_LAUNCH is the shape the parity test of the full ensemble uses.
 MAIN_LAUNCH = (512, False, 1)
