@@ -664,8 +664,8 @@ int upload(lbm_handle* h) {
   h->dev.step_near = h->alloc<int>(2 * nstep, rc);
   h->d_bmark = h->alloc<BeadState>(h->beads.size(), rc);
   if (rc != LBM_OK) return h->fail(rc, "device allocation for markers failed");
-  // no near tiles until a step's are marked
-  rc = h->hip(hipMemset(h->dev.near_range, 0, sizeof(NearRange) * 2 * h->beads.size()), "hipMemset");
+  const std::vector<NearRange> none(2 * h->beads.size());  // no near tiles until a step's are marked
+  put(h->dev.near_range, none.data(), sizeof(NearRange) * none.size());
   put(d_patch, P.head.data(), sizeof(int) * P.head.size());
   put(d_patch_marker, P.marker.data(), sizeof(int) * P.marker.size());
   put(d_patch_tri, P.tri.data(), sizeof(int) * P.tri.size());
