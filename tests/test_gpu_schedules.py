@@ -80,6 +80,32 @@ def test_launch_shapes_of_a_two_stream_box(storage):
             _same(lat, ref, (shape, graphs))
 
 
+@pytest.mark.parametrize("storage", [lbmib.FP32_SHIFTED, lbmib.FP32_INPLACE, lbmib.FP32_PLAIN])
+def test_averages_and_restarts_of_a_two_stream_box(storage, tmp_path):
+    case = _box(22, 0)
+    ref = lbmib.from_workload(case, storage=storage, use_graphs=False)
+    ref.average_begin(3)
+    ref.step(45)
+    mean, samples = ref.average_velocity()
+    path = str(tmp_path / "ck.bin")
+    for shape in ((512, False, 0), (512, False, 1), (256, True, 2), (256, False, -1)):
+        print("shape", shape, flush=True)
+        lat = lbmib.from_workload(case, storage=storage)
+        lat.set_stream_collide_launch(*shape)
+        lat.average_begin(3)
+        lat.step(13)
+        lat.step(32)
+        got, n = lat.average_velocity()
+        assert n == samples and np.array_equal(got, mean), shape
+        _same(lat, ref, shape)
+        lat.save(path)
+        lat.step(7)
+        other = lbmib.from_workload(case, storage=storage)
+        other.load(path)
+        other.step(7)
+        _same(lat, other, shape)
+
+
 def test_launch_shapes_of_a_large_batch():
     ens = wl.ensemble(seed=7, nboxes=43)
     for i, b in enumerate(ens["boxes"]):
